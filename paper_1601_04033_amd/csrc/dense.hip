@@ -46,6 +46,8 @@ constexpr int kLaneBlock = 256;
 constexpr int kLaneBatch = 3;
 constexpr int kPushBatch = 4;      // the pass with a push: 647 against 694 us at 25M with 3, 28.1 against 29.3 ms at 1e9
 constexpr int kSgdBatch = 4;       // SASGD and synchronous SGD
+constexpr int kIeeeBatch = 4;      // the IEEE passes in the short sequences (short_updates)
+static_assert(kIeeeBatch == kPushBatch, "the pass with a push hands its first batch to short_updates");
 
 unsigned lane_grid(int64_t P) { return static_cast<unsigned>((P + kLaneBlock - 1) / kLaneBlock); }
 
@@ -70,6 +72,18 @@ __device__ __forceinline__ void fasgd_step4(f4& th, f4& n, f4& b, f4& v, const f
         fasgd_step<MODE>(t, nn, bb, vv, g[c], coef, h);
         th[c] = t; n[c] = nn; b[c] = bb; v[c] = vv;
     }
+}
+
+// One update of the IEEE passes: SHORT, the short sequences without a look at
+// each divisor (see v_in_short_range); otherwise fasgd_step.
+template <int MODE, bool SHORT>
+__device__ __forceinline__ void pass_step(float& th, float& n, float& b, float& v, float g, float coef,
+                                          const Hyper& h)
+{
+    if constexpr (SHORT && (MODE & MATH_FAST) == 0)   // SHORT is never set in FAST mode
+        fasgd_step_short<MODE>(th, n, b, v, g, coef, h);
+    else
+        fasgd_step<MODE>(th, n, b, v, g, coef, h);
 }
 
 unsigned grid_for(int64_t items)
@@ -436,6 +450,79 @@ __device__ __forceinline__ void stage_segment(int32_t e_idx, float e_val, bool e
     block_barrier_lds();
 }
 
+// Whether the wave runs an IEEE pass in the short sequences (wave-uniform).
+// A lane whose v is outside v_in_short_range sends its wave to fasgd_step,
+// which looks at each divisor.
+template <int MODE>
+__device__ __forceinline__ bool short_pass(float v, const Hyper& h)
+{
+    if constexpr ((MODE & MATH_FAST) != 0) return false;
+    return __ballot(!v_in_short_range(v, h)) == 0;
+}
+
+// The K >= kIeeeBatch gradients of an IEEE pass in the short sequences, the
+// first kIeeeBatch of them loaded in g.  The vector ALU bounds this pass
+// about as much as HBM does, so the next batch is loaded before the one in
+// hand is applied (the FAST pass, which only streams, is slower that way).
+// Measured at 25M parameters, K = 32, same box: 796 us with the sequences
+// and divisor checks this replaced, 760 us with the new ones in batches of 3
+// (4: 717, 6: 711, 8: 718), 668 us with the next batch of 4 loaded ahead
+// (2: 721, 3: 679, 6: 674); the FAST pass takes 645 us.
+template <int MODE>
+__device__ __forceinline__ void short_updates(const DenseArgs& a, int64_t j, const float (&g0)[kIeeeBatch], float& th,
+                                              float& n, float& b, float& v)
+{
+    if constexpr ((MODE & MATH_FAST) == 0) {
+        const Hyper h = a.h;
+        const int K = a.K;
+        float g[kIeeeBatch];
+#pragma unroll
+        for (int u = 0; u < kIeeeBatch; ++u) g[u] = g0[u];
+        int k = 0;
+        for (; k + 2 * kIeeeBatch <= K; k += kIeeeBatch) {
+            float next[kIeeeBatch];
+#pragma unroll
+            for (int u = 0; u < kIeeeBatch; ++u) next[u] = ldnt(a.grad[k + kIeeeBatch + u] + j);
+            __builtin_amdgcn_sched_barrier(0);   // the loads stay ahead of the updates
+#pragma unroll
+            for (int u = 0; u < kIeeeBatch; ++u) fasgd_step_short<MODE>(th, n, b, v, g[u], a.coef[k + u], h);
+#pragma unroll
+            for (int u = 0; u < kIeeeBatch; ++u) g[u] = next[u];
+        }
+#pragma unroll
+        for (int u = 0; u < kIeeeBatch; ++u) fasgd_step_short<MODE>(th, n, b, v, g[u], a.coef[k + u], h);
+        for (k += kIeeeBatch; k < K; ++k) fasgd_step_short<MODE>(th, n, b, v, ldnt(a.grad[k] + j), a.coef[k], h);
+    }
+}
+
+// The push (where the parameter is listed), then the K gradients, the first
+// k0 of them loaded already.
+template <int MODE, bool SHORT>
+__device__ __forceinline__ void push_updates(const DenseArgs& a, const PushArgs& p, int64_t jl, bool listed,
+                                             float push_g, const float (&g0)[kPushBatch], int k0, float& th,
+                                             float& n, float& b, float& v)
+{
+    const Hyper h = a.h;
+    const int K = a.K;
+    if (listed) pass_step<MODE, SHORT>(th, n, b, v, push_g, p.coef, h);
+    if (SHORT && k0 == kPushBatch) {
+        short_updates<MODE>(a, jl, g0, th, n, b, v);
+        return;
+    }
+#pragma unroll
+    for (int u = 0; u < kPushBatch; ++u)
+        if (u < k0) pass_step<MODE, SHORT>(th, n, b, v, g0[u], a.coef[u], h);
+    int k = k0;
+    for (; k + kPushBatch <= K; k += kPushBatch) {
+        float g[kPushBatch];
+#pragma unroll
+        for (int u = 0; u < kPushBatch; ++u) g[u] = ldnt(a.grad[k + u] + jl);
+#pragma unroll
+        for (int u = 0; u < kPushBatch; ++u) pass_step<MODE, SHORT>(th, n, b, v, g[u], a.coef[k + u], h);
+    }
+    for (; k < K; ++k) pass_step<MODE, SHORT>(th, n, b, v, ldnt(a.grad[k] + jl), a.coef[k], h);
+}
+
 // The pass with a compacted push applied ahead of the K gradients, one
 // parameter per thread (any 4-byte alignment).  Block s owns list-index
 // segment s (kPushSeg parameters).  Thread t loads entry lo + t of the
@@ -477,19 +564,17 @@ __global__ __launch_bounds__(kLaneBlock) void fasgd_dense_push_lane(const DenseA
 #pragma unroll
     for (int u = 0; u < kPushBatch; ++u) g0[u] = ldnt(a.grad[u < k0 ? u : 0] + jl);
     stage_segment(e_idx, e_val, entry, first, a.P, s_val, s_flag);
-    if (s_flag[t]) fasgd_step<MODE>(th, n, b, v, s_val[t], p.coef, h);
-#pragma unroll
-    for (int u = 0; u < kPushBatch; ++u)
-        if (u < k0) fasgd_step<MODE>(th, n, b, v, g0[u], a.coef[u], h);
-    int k = k0;
-    for (; k + kPushBatch <= K; k += kPushBatch) {
-        float g[kPushBatch];
-#pragma unroll
-        for (int u = 0; u < kPushBatch; ++u) g[u] = ldnt(a.grad[k + u] + jl);
-#pragma unroll
-        for (int u = 0; u < kPushBatch; ++u) fasgd_step<MODE>(th, n, b, v, g[u], a.coef[k + u], h);
+    const bool listed = s_flag[t] != 0;
+    const float push_g = s_val[t];
+    if (short_pass<MODE>(v, h)) {
+        push_updates<MODE, true>(a, p, jl, listed, push_g, g0, k0, th, n, b, v);
+        if (__builtin_expect(__ballot(v != v) != 0, 0)) {   // an infinite or NaN x: the pass again, divisor by divisor
+            th = a.theta[jl]; n = a.n[jl]; b = a.b[jl]; v = a.v[jl];
+            push_updates<MODE, false>(a, p, jl, listed, push_g, g0, k0, th, n, b, v);
+        }
+    } else {
+        push_updates<MODE, false>(a, p, jl, listed, push_g, g0, k0, th, n, b, v);
     }
-    for (; k < K; ++k) fasgd_step<MODE>(th, n, b, v, ldnt(a.grad[k] + jl), a.coef[k], h);
     if (own) {
         stnt(a.theta + j, th);
         stnt(a.n + j, n);
@@ -564,25 +649,46 @@ __global__ __launch_bounds__(kLaneBlock) void fasgd_cached_push_lane(const Dense
     stnt(a.v + j, v);
 }
 
-// K-fused FASGD, one parameter per thread (any 4-byte alignment): the pass
-// for every P below kMaxScalarItems.
-template <int MODE>
-__global__ __launch_bounds__(kLaneBlock) void fasgd_dense_lane(const DenseArgs a)
+template <int MODE, bool SHORT>
+__device__ __forceinline__ void lane_updates(const DenseArgs& a, int64_t j, float& th, float& n, float& b, float& v)
 {
     const Hyper h = a.h;
     const int K = a.K;
-    const int64_t j = static_cast<int64_t>(blockIdx.x) * kLaneBlock + threadIdx.x;
-    if (j >= a.P) return;
-    float th = ldnt(a.theta + j), n = ldnt(a.n + j), b = ldnt(a.b + j), v = ldnt(a.v + j);
     int k = 0;
+    if (SHORT && K >= kIeeeBatch) {
+        float g[kIeeeBatch];
+#pragma unroll
+        for (int u = 0; u < kIeeeBatch; ++u) g[u] = ldnt(a.grad[u] + j);
+        short_updates<MODE>(a, j, g, th, n, b, v);
+        return;
+    }
     for (; k + kLaneBatch <= K; k += kLaneBatch) {
         float g[kLaneBatch];
 #pragma unroll
         for (int u = 0; u < kLaneBatch; ++u) g[u] = ldnt(a.grad[k + u] + j);
 #pragma unroll
-        for (int u = 0; u < kLaneBatch; ++u) fasgd_step<MODE>(th, n, b, v, g[u], a.coef[k + u], h);
+        for (int u = 0; u < kLaneBatch; ++u) pass_step<MODE, SHORT>(th, n, b, v, g[u], a.coef[k + u], h);
     }
-    for (; k < K; ++k) fasgd_step<MODE>(th, n, b, v, ldnt(a.grad[k] + j), a.coef[k], h);
+    for (; k < K; ++k) pass_step<MODE, SHORT>(th, n, b, v, ldnt(a.grad[k] + j), a.coef[k], h);
+}
+
+// K-fused FASGD, one parameter per thread (any 4-byte alignment): the pass
+// for every P below kMaxScalarItems.
+template <int MODE>
+__global__ __launch_bounds__(kLaneBlock) void fasgd_dense_lane(const DenseArgs a)
+{
+    const int64_t j = static_cast<int64_t>(blockIdx.x) * kLaneBlock + threadIdx.x;
+    if (j >= a.P) return;
+    float th = ldnt(a.theta + j), n = ldnt(a.n + j), b = ldnt(a.b + j), v = ldnt(a.v + j);
+    if (short_pass<MODE>(v, a.h)) {
+        lane_updates<MODE, true>(a, j, th, n, b, v);
+        if (__builtin_expect(__ballot(v != v) != 0, 0)) {   // an infinite or NaN x: the pass again, divisor by divisor
+            th = a.theta[j]; n = a.n[j]; b = a.b[j]; v = a.v[j];
+            lane_updates<MODE, false>(a, j, th, n, b, v);
+        }
+    } else {
+        lane_updates<MODE, false>(a, j, th, n, b, v);
+    }
     stnt(a.theta + j, th);
     stnt(a.n + j, n);
     stnt(a.b + j, b);

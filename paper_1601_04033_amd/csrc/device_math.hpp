@@ -26,58 +26,67 @@ struct Hyper {
     float alpha;   // master rate
     int32_t rn_short;   // IEEE mode: eps >= 2^-96 and 2^-20 <= |alpha| < 2^20 (set by the host), so the
                         // short correctly rounded sequences below hold; otherwise the general ones run
+    float v_lo;         // IEEE mode: with rn_short and v_lo <= v <= kShortVMax at the start of a pass, every
+                        // divisor v tau of the pass stays in the short division's range (see v_in_short_range);
+                        // +inf where that cannot be said
 };
 
 // Correctly rounded square root, reciprocal and division in fewer
 // instructions than the general sequences, for the operand ranges the IEEE
 // update meets once the host has checked eps and alpha.  Each starts from
-// the hardware estimate (within 1 ulp) and corrects it with exact residuals
-// computed by fused multiply-adds.  fasgd_check_ieee_sequences compares them
-// with the general sequences bit for bit, exhaustively over their ranges.
+// a hardware estimate (within 1 ulp) and corrects it with residuals that one
+// fused multiply-add computes exactly.  fasgd_check_ieee_sequences compares
+// them with the general sequences bit for bit, exhaustively over their ranges.
 //
-// sqrt(x), x >= 2^-96, +inf or NaN: of the estimate s and its neighbours
-// s-, s+ (one ulp away), the residuals x - s- s and x - s+ s tell on which
-// side of each midpoint the root lies (a root of a float is never exactly a
-// midpoint); at x >= 2^-96 the residuals are normal numbers, so their signs
-// are exact.
+// sqrt(x), 2^-96 <= x finite: from y ~ 1/sqrt(x), the estimate g = x y and
+// Markstein's last step g + (x - g g) y/2.  At x >= 2^-96 the residual's last
+// bit lies at or above 2^-142, so it is exact.  4 instructions beside the
+// estimate, against 8 for comparing the residuals of the hardware root's two
+// neighbours.
+// x = +inf gives NaN (0 times inf), which the callers look for.
 __device__ __forceinline__ float sqrt_rn_short(float x)
 {
-    float s = __builtin_amdgcn_sqrtf(x);
-    const float sm = __int_as_float(__float_as_int(s) - 1);
-    const float sp = __int_as_float(__float_as_int(s) + 1);
-    const float rm = fmaf(-sm, s, x);
-    const float rp = fmaf(-sp, s, x);
-    s = rm <= 0.0f ? sm : s;
-    s = rp > 0.0f ? sp : s;
-    return s;
+    const float y = __builtin_amdgcn_rsqf(x);
+    const float g = x * y;
+    return fmaf(fmaf(-g, g, x), 0.5f * y, g);
 }
 
-// 1/r for r = sqrt_rn_short(x), x >= 2^-96 (r in [2^-48, 2^64], +inf or
-// NaN): one Newton step y + y (1 - r y) with the residual exact in the fma;
-// the fix-up gives 1/inf = 0.
+// 1/r for r = sqrt_rn_short(x), 2^-96 <= x finite (r in [2^-48, 2^64]): one
+// Newton step y + y (1 - r y) with the residual exact in the fma.  (Starting
+// from the 1/sqrt(x) above instead of an estimate of its own fails where r's
+// significand is all ones: 1/r then lies just above a midpoint.)
 __device__ __forceinline__ float rcp_of_root_rn_short(float r)
 {
     const float y0 = __builtin_amdgcn_rcpf(r);
-    const float e = fmaf(-r, y0, 1.0f);
-    return __builtin_amdgcn_div_fixupf(fmaf(e, y0, y0), r, 1.0f);
+    return fmaf(fmaf(-r, y0, 1.0f), y0, y0);
 }
 
-// a / d for 2^-20 <= |a| < 2^20: the reciprocal as above, the quotient
-// q0 = a y, then q0 + y (a - d q0) with the remainder exact in the fma
-// (Markstein's correction).  Lanes whose |d| lies outside [2^-100, 2^100]
-// (zero, subnormal, huge, infinite or NaN divisors) take the general division.
+// a / d for 2^-20 <= |a| < 2^20 and |d| in [2^-100, 2^100]: the reciprocal
+// as above, the quotient q0 = a y, then q0 + y (a - d q0) with the remainder
+// exact in the fma (Markstein's correction).
+constexpr float kShortDMin = 0x1p-100f, kShortDMax = 0x1p100f;
+__device__ __forceinline__ bool d_in_short_range(float d)
+{
+    return __builtin_fabsf(d) >= kShortDMin && __builtin_fabsf(d) <= kShortDMax;
+}
 __device__ __forceinline__ float div_rn_short(float a, float d)
 {
     const float y0 = __builtin_amdgcn_rcpf(d);
-    const float e = fmaf(-d, y0, 1.0f);
-    const float y = fmaf(e, y0, y0);
+    const float y = fmaf(fmaf(-d, y0, 1.0f), y0, y0);
     const float q0 = a * y;
-    const float r = fmaf(-d, q0, a);
-    float q = fmaf(r, y, q0);
-    const bool in_range = __builtin_fabsf(d) >= 0x1p-100f && __builtin_fabsf(d) <= 0x1p100f;
-    if (__builtin_expect(__ballot(!in_range) != 0, 0)) q = in_range ? q : a / d;
-    return q;
+    return fmaf(fmaf(-d, q0, a), y, q0);
 }
+
+// Whether a pass may run the short sequences without looking at each divisor.
+// With eps >= 2^-96 and x = max(n - b^2, 0) + eps finite, what v averages
+// (1/sqrt(x) or sqrt(x)) lies in [2^-64, 2^64].  v is a convex combination of
+// it and the old v, so from v_lo = 0 <= v <= 2^60 it stays at or above
+// (1 - beta) 2^-64 >= 2^-88 and below 2^65 (beta < 1; at beta = 1, v does not
+// change and v_lo = 2^-60), and v tau (1 <= tau <= 2^31) inside [2^-100,
+// 2^100].  An infinite or NaN x makes v NaN, and v stays NaN, so one look at
+// v after the pass finds it.
+constexpr float kShortVMax = 0x1p60f;
+__device__ __forceinline__ bool v_in_short_range(float v, const Hyper& h) { return v >= h.v_lo && v <= kShortVMax; }
 
 // One parameter, one gradient: the FASGD update of Sec. 2.2.
 //   n <- gamma n + (1-gamma) g^2 ; b <- gamma b + (1-gamma) g
@@ -104,16 +113,43 @@ __device__ __forceinline__ void fasgd_step(float& th, float& n, float& b, float&
         v = fmaf(h.beta, v, h.omb * s);
         th = fmaf(-(coef * __builtin_amdgcn_rcpf(v)), g, th);
     } else if (h.rn_short) {
-        // the same correctly rounded operations as below, in the short sequences
+        // the same correctly rounded operations as below, in the short
+        // sequences; lanes with a divisor out of their range (an infinite or
+        // NaN x among them: it makes v NaN) take the general ones
         const float r = sqrt_rn_short(x);
-        const float s = prose ? r : rcp_of_root_rn_short(r);
-        v = fmaf(h.beta, v, h.omb * s);
-        th = fmaf(-div_rn_short(h.alpha, v * coef), g, th);
+        float vn = fmaf(h.beta, v, h.omb * (prose ? r : rcp_of_root_rn_short(r)));
+        float q = div_rn_short(h.alpha, vn * coef);
+        const bool in_range = d_in_short_range(vn * coef);
+        if (__builtin_expect(__ballot(!in_range) != 0, 0)) {
+            if (!in_range) {
+                vn = fmaf(h.beta, v, h.omb * (prose ? sqrtf(x) : 1.0f / sqrtf(x)));
+                q = h.alpha / (vn * coef);
+            }
+        }
+        v = vn;
+        th = fmaf(-q, g, th);
     } else {
         const float s = prose ? sqrtf(x) : 1.0f / sqrtf(x);
         v = fmaf(h.beta, v, h.omb * s);
         th = fmaf(-(h.alpha / (v * coef)), g, th);
     }
+}
+
+// The IEEE update in the short sequences alone, for a pass whose v was in
+// v_in_short_range at its start and whose v is checked for NaN at its end.
+template <int VARIANT>
+__device__ __forceinline__ void fasgd_step_short(float& th, float& n, float& b, float& v, float g, float coef,
+                                                 const Hyper& h)
+{
+    static_assert((VARIANT & MATH_FAST) == 0, "IEEE mode");
+    constexpr bool prose = (VARIANT & V_PROSE) != 0;
+    const float a = h.omg * g;
+    n = fmaf(h.gamma, n, a * g);
+    b = fmaf(h.gamma, b, a);
+    const float x = fmaxf(fmaf(-b, b, n), 0.0f) + h.eps;
+    const float r = sqrt_rn_short(x);
+    v = fmaf(h.beta, v, h.omb * (prose ? r : rcp_of_root_rn_short(r)));
+    th = fmaf(-div_rn_short(h.alpha, v * coef), g, th);
 }
 
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11).  Per round, words 0 and

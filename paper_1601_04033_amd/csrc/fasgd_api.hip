@@ -102,6 +102,15 @@ bool ieee_short_ok(float eps, float alpha)
     return isfinite(eps) && eps >= 0x1p-96f && fabsf(alpha) >= 0x1p-20f && fabsf(alpha) < 0x1p20f;
 }
 
+// Hyper::v_lo: what v must be at least, at the start of a pass, for the
+// short sequences to hold over the whole pass.
+float short_v_lo(const fasgd::Hyper& h)
+{
+    if (!h.rn_short) return INFINITY;
+    if (h.beta >= 0.0f && h.omb >= 0x1p-24f && h.omb <= 1.0f) return 0.0f;
+    return h.beta == 1.0f ? 0x1p-60f : INFINITY;
+}
+
 fasgd::Hyper hyper_of(const fasgd_state* st)
 {
     fasgd::Hyper h;
@@ -112,6 +121,7 @@ fasgd::Hyper hyper_of(const fasgd_state* st)
     h.eps = st->eps;
     h.alpha = st->alpha;
     h.rn_short = ieee_short_ok(st->eps, st->alpha) ? 1 : 0;
+    h.v_lo = short_v_lo(h);
     return h;
 }
 
@@ -897,6 +907,7 @@ fasgd_status fasgd_check_ieee_sequences(float gamma, float beta, float eps, floa
     h.eps = eps;
     h.alpha = alpha;
     h.rn_short = 1;
+    h.v_lo = short_v_lo(h);
     const hipError_t e = fasgd::launch_check_ieee(h, seed, n_updates, d_mismatches, stream);
     if (e != hipSuccess) return hip_fail(e, "fasgd_check_ieee_sequences");
     return ok();

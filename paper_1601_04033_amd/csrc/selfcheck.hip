@@ -1,11 +1,15 @@
 // Device self-check of the IEEE update's short correctly rounded sequences
 // (sqrt_rn_short, rcp_of_root_rn_short, div_rn_short) against the general
 // sequences the compiler emits for sqrtf and '/', bit for bit:
-//   - the square root and the reciprocal of the root over every float
-//     x >= 2^-96 (+inf and the positive NaNs included);
-//   - the division alpha / d over every one of the 2^32 bit patterns of d;
+//   - the square root and the reciprocal of the root over every finite float
+//     x >= 2^-96 (an infinite or NaN x must give a NaN root, by which the
+//     update finds it);
+//   - the division alpha / d over every d of its range, with either sign, and
+//     every other of the 2^32 bit patterns of d found to be out of range;
 //   - whole updates (fasgd_step, IEEE mode, both readings of v) on
-//     pseudo-random states, with rn_short set and cleared.
+//     pseudo-random states, infinities and NaNs among them, with rn_short set
+//     and cleared.  Where v starts inside v_in_short_range, the unguarded
+//     fasgd_step_short must agree as well or leave v NaN.
 // NaN results compare equal to NaN results whatever their payloads.
 #include "kernels.hpp"
 
@@ -32,7 +36,7 @@ __global__ __launch_bounds__(kCheckBlock) void clear_counts(unsigned long long* 
     if (threadIdx.x < kIeeeChecks) counts[threadIdx.x] = 0ull;
 }
 
-// counts[0]: sqrt, counts[1]: 1 / sqrt (two roundings), x in [2^-96, NaN]
+// counts[0]: sqrt, counts[1]: 1 / sqrt (two roundings), x in [2^-96, max]
 __global__ __launch_bounds__(kCheckBlock) void check_roots(unsigned long long* counts)
 {
     constexpr uint64_t lo = 0x0F800000u;   // 2^-96
@@ -41,6 +45,10 @@ __global__ __launch_bounds__(kCheckBlock) void check_roots(unsigned long long* c
     for (uint64_t i = lo + thread_index(); i <= hi; i += thread_count()) {
         const float x = __uint_as_float(static_cast<uint32_t>(i));
         const float r = sqrt_rn_short(x);
+        if (i >= 0x7F800000u) {   // +inf, NaN
+            bad_root += r == r;
+            continue;
+        }
         const float want = sqrtf(x);
         bad_root += !same_bits(r, want);
         bad_rcp += !same_bits(rcp_of_root_rn_short(r), 1.0f / want);
@@ -49,13 +57,15 @@ __global__ __launch_bounds__(kCheckBlock) void check_roots(unsigned long long* c
     if (bad_rcp) atomicAdd(counts + 1, bad_rcp);
 }
 
-// counts[2]: alpha / d over every bit pattern of d
+// counts[2]: alpha / d over every bit pattern of d in range
 __global__ __launch_bounds__(kCheckBlock) void check_division(float alpha, unsigned long long* counts)
 {
     unsigned long long bad = 0;
     for (uint64_t i = thread_index(); i <= 0xFFFFFFFFull; i += thread_count()) {
         const float d = __uint_as_float(static_cast<uint32_t>(i));
-        bad += !same_bits(div_rn_short(alpha, d), alpha / d);
+        const uint32_t mag = static_cast<uint32_t>(i) & 0x7FFFFFFFu;
+        const bool in = mag >= 0x0D800000u && mag <= 0x71800000u;   // 2^-100, 2^100
+        bad += in != d_in_short_range(d) || (in && !same_bits(div_rn_short(alpha, d), alpha / d));
     }
     if (bad) atomicAdd(counts + 2, bad);
 }
@@ -97,9 +107,14 @@ __global__ __launch_bounds__(kCheckBlock) void check_updates(Hyper h, uint64_t s
         const float g = draw(k + 4, 1e-2f);
         const float coef = 1.0f + static_cast<float>(mix32(k + 5) & 1023u);   // tau
         float th2 = th, n2 = n, b2 = b, v2 = v;
+        float th3 = th, n3 = n, b3 = b, v3 = v;
+        const bool in_range = v_in_short_range(v, hs);
         fasgd_step<VARIANT>(th, n, b, v, g, coef, hs);
         fasgd_step<VARIANT>(th2, n2, b2, v2, g, coef, hg);
         bad += !(same_bits(th, th2) && same_bits(n, n2) && same_bits(b, b2) && same_bits(v, v2));
+        fasgd_step_short<VARIANT>(th3, n3, b3, v3, g, coef, hs);
+        if (in_range && v3 == v3)
+            bad += !(same_bits(th3, th2) && same_bits(n3, n2) && same_bits(b3, b2) && same_bits(v3, v2));
     }
     if (bad) atomicAdd(counts + 3, bad);
 }
