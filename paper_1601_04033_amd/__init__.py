@@ -11,6 +11,10 @@ keep the C ABI's names (include/fasgd.h):
 
 There is no fallback: if libfasgd.so is missing or cannot be loaded, every
 call raises.
+
+The per-arrival calls marshal plain arguments natively (csrc/marshal.cpp,
+module _marshal); arguments that are not plain there take the general way
+below them, which converts or rejects them with the same library call.
 """
 from __future__ import annotations
 
@@ -116,15 +120,38 @@ def load_library(path: Optional[str] = None):
     return lib
 
 
+_calls = None     # module _marshal, once bound
+
+
+def _current_stream() -> int:
+    """Handle of torch's current stream."""
+    import torch
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
+def _native():
+    """The native marshalling module, bound to the loaded library."""
+    global _calls
+    if _calls is None:
+        lib = load_library()
+        import torch  # noqa: F401  (the module resolves against torch's libraries)
+        try:
+            from . import _marshal as m
+        except ImportError as e:
+            raise OSError(f"_marshal.so is not built or does not load ({e}); run __graft_entry__.build()") from e
+        m.bind([ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in m.ENTRY_POINTS], _current_stream)
+        _calls = m
+    return _calls
+
+
 def _check(rc: int):
     if rc != 0:
         raise FasgdError(rc, load_library().fasgd_last_error().decode())
 
 
 def _stream(stream) -> int:
-    import torch
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return _current_stream()
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
 
 
@@ -242,6 +269,9 @@ def _dense_args(state: State, grads: Sequence, clients: Sequence[int], grad_ts: 
 def fasgd_apply_updates(state: State, grads: Sequence, clients: Sequence[int], grad_ts: Sequence[int],
                         stream=None) -> None:
     """Apply K gradients (arrival order) with the FASGD rule; T advances by K."""
+    rc = (_calls or _native()).fasgd_apply_updates(state.c, grads, clients, grad_ts, stream)
+    if rc is not None:
+        return _check(rc) if rc else None
     ptrs, c, ts, K = _dense_args(state, grads, clients, grad_ts)
     _check(load_library().fasgd_apply_updates(ctypes.byref(state.c), ptrs, c, ts, K, _stream(stream)))
 
@@ -249,6 +279,9 @@ def fasgd_apply_updates(state: State, grads: Sequence, clients: Sequence[int], g
 def sasgd_apply_updates(state: State, grads: Sequence, clients: Sequence[int], grad_ts: Sequence[int],
                         stream=None) -> None:
     """Apply K gradients with the SASGD rate alpha / max(tau, 1); T advances by K."""
+    rc = (_calls or _native()).sasgd_apply_updates(state.c, grads, clients, grad_ts, stream)
+    if rc is not None:
+        return _check(rc) if rc else None
     ptrs, c, ts, K = _dense_args(state, grads, clients, grad_ts)
     _check(load_library().sasgd_apply_updates(ctypes.byref(state.c), ptrs, c, ts, K, _stream(stream)))
 
@@ -268,6 +301,10 @@ def bfasgd_select_compact(state: State, grad, c: float, eps_c: float, seed: int,
     number transmitted goes to d_count (int64 [1], device).  seg_start
     (optional, int32 [bfasgd_list_index_length(P)], values < 2^31) receives
     the list's index: the position of each 256-parameter segment's first entry."""
+    rc = (_calls or _native()).bfasgd_select_compact(state.c, grad, c, eps_c, seed, T, client, out_idx, out_val, d_count,
+                                                   workspace, seg_start, stream)
+    if rc is not None:
+        return _check(rc) if rc else None
     import torch
     cap = out_idx.numel()
     if out_val.numel() != cap:
@@ -316,6 +353,10 @@ def fasgd_apply_with_push(state: State, push_idx, push_val, push_count, push_seg
                           stream=None) -> None:
     """One pass: the compacted push (at T, as bfasgd_apply_sparse) and then the K
     gradients (at T + 1 ... T + K, as fasgd_apply_updates).  T advances by K + 1."""
+    rc = (_calls or _native()).fasgd_apply_with_push(state.c, push_idx, push_val, push_count, push_seg_start, push_client,
+                                                   push_grad_ts, grads, clients, grad_ts, stream)
+    if rc is not None:
+        return _check(rc) if rc else None
     import torch
     cap = push_idx.numel()
     if push_val.numel() != cap:
@@ -356,6 +397,10 @@ def bfasgd_select_compact_batch(state: State, grads: Sequence, c: float, eps_c: 
     from v as it stands now.  out_idx / out_val: [B, capacity]; d_count: [B];
     seg_start (optional): int32 [B, bfasgd_list_index_length(P)]; workspace:
     at least B * bfasgd_workspace_bytes(P) bytes."""
+    rc = (_calls or _native()).bfasgd_select_compact_batch(state.c, grads, c, eps_c, seed, T, clients, out_idx, out_val, d_count,
+                                                         workspace, seg_start, stream)
+    if rc is not None:
+        return _check(rc) if rc else None
     import torch
     B = len(grads)
     if len(T) != B or len(clients) != B:
@@ -382,6 +427,9 @@ def fasgd_apply_pushes(state: State, idx, val, d_count, seg_start, clients: Sequ
                        stream=None) -> None:
     """B compacted pushes ([B, capacity] lists with their [B, L] index) in one
     pass, as B bfasgd_apply_sparse calls in order; T advances by B."""
+    rc = (_calls or _native()).fasgd_apply_pushes(state.c, idx, val, d_count, seg_start, clients, grad_ts, stream)
+    if rc is not None:
+        return _check(rc) if rc else None
     import torch
     B = len(clients)
     if len(grad_ts) != B:
@@ -407,6 +455,11 @@ def fasgd_apply_with_push_and_select(state: State, push_idx, push_val, push_coun
     bfasgd_select_compact at the timestamp after the pass, from the v the
     pass leaves) in one call; the output list may be the input push's
     buffers.  T advances by K + 1."""
+    rc = (_calls or _native()).fasgd_apply_with_push_and_select(
+        state.c, push_idx, push_val, push_count, push_seg_start, push_client, push_grad_ts, grads, clients, grad_ts,
+        next_grad, next_client, c, eps_c, seed, out_idx, out_val, out_count, out_seg_start, workspace, stream)
+    if rc is not None:
+        return _check(rc) if rc else None
     import torch
     cap = push_idx.numel()
     if push_val.numel() != cap:
@@ -471,6 +524,9 @@ def fasgd_check_ieee_sequences(gamma: float, beta: float, eps: float, alpha: flo
 
 def bfasgd_apply_sparse(state: State, idx, val, d_count, client: int, grad_ts: int, stream=None) -> None:
     """FASGD update of the listed parameters (first *d_count entries); T advances by one."""
+    rc = (_calls or _native()).bfasgd_apply_sparse(state.c, idx, val, d_count, client, grad_ts, stream)
+    if rc is not None:
+        return _check(rc) if rc else None
     import torch
     cap = idx.numel()
     if val.numel() != cap:
@@ -499,6 +555,9 @@ def bfasgd_apply_cached(state: State, idx, val, d_count, cache, client: int, gra
     """Push with dropped values re-applied from the client's cache (updated in
     place).  seg_start (optional): the list's index from the selection, with
     which the list is merged into the cache inside the one pass."""
+    rc = (_calls or _native()).bfasgd_apply_cached(state.c, idx, val, d_count, cache, client, grad_ts, seg_start, stream)
+    if rc is not None:
+        return _check(rc) if rc else None
     import torch
     cap = idx.numel()
     if val.numel() != cap:
@@ -516,6 +575,9 @@ def bfasgd_apply_fetch(theta_client, idx, val, d_count, seg_start=None, stream=N
     """Copy the listed values into a client's copy of theta.  seg_start
     (optional): the list's index, with which segments holding an entry are
     rewritten whole (faster when most segments hold one)."""
+    rc = (_calls or _native()).bfasgd_apply_fetch(theta_client, idx, val, d_count, seg_start, stream)
+    if rc is not None:
+        return _check(rc) if rc else None
     import torch
     cap = idx.numel()
     if val.numel() != cap:
@@ -542,6 +604,9 @@ def bfasgd_decide_segments(state: State, seg, c: float, eps_c: float, seed: int,
                            d_transmit, workspace, stream=None) -> None:
     """Paper-literal decisions, one per segment of `seg` (host offsets, S + 1
     of them), into d_transmit (device uint8 [S])."""
+    rc = (_calls or _native()).bfasgd_decide_segments(state.c, seg, c, eps_c, seed, T, client, d_transmit, workspace, stream)
+    if rc is not None:
+        return _check(rc) if rc else None
     import torch
     arr, ptr, S = _seg_array(seg)
     if d_transmit.numel() != S:
@@ -555,6 +620,9 @@ def bfasgd_decide_segments(state: State, seg, c: float, eps_c: float, seed: int,
 
 def bfasgd_apply_segments(state: State, grad, seg, d_transmit, client: int, grad_ts: int, stream=None) -> None:
     """FASGD update on the transmitted segments; T advances by one."""
+    rc = (_calls or _native()).bfasgd_apply_segments(state.c, grad, seg, d_transmit, client, grad_ts, stream)
+    if rc is not None:
+        return _check(rc) if rc else None
     import torch
     arr, ptr, S = _seg_array(seg)
     if grad.numel() != state.P:

@@ -1,8 +1,10 @@
-"""Build libfasgd.so (HIP, gfx950) in-tree with hipcc."""
+"""Build libfasgd.so (HIP, gfx950) with hipcc and the binding's _marshal.so (host C++ against torch's headers) with
+g++, both in-tree."""
 import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -10,6 +12,8 @@ CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libfasgd.so")
 SOURCES = ["fasgd_api.hip", "dense.hip", "bfasgd.hip", "segments.hip", "pushes.hip", "selfcheck.hip", "anchor.hip"]
+
+MARSHAL = os.path.join(PKG, "_marshal.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
@@ -42,7 +46,26 @@ def build(verbose: bool = False, extra_flags=()) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
     os.replace(tmp, LIB)
+    build_marshal(verbose)
     return LIB
+
+
+def build_marshal(verbose: bool = False) -> str:
+    """The native argument marshalling of the binding (csrc/marshal.cpp)."""
+    import torch
+    from torch.utils import cpp_extension
+    inc = [f"-I{d}" for d in (os.path.join(ROOT, "include"), *cpp_extension.include_paths(),
+                              sysconfig.get_paths()["include"], "/opt/rocm/include")]
+    tmp = MARSHAL + ".tmp"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *inc,
+           os.path.join(CSRC, "marshal.cpp"), "-o", tmp, *[f"-L{d}" for d in cpp_extension.library_paths()],
+           "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, MARSHAL)
+    return MARSHAL
 
 
 if __name__ == "__main__":

@@ -1,0 +1,253 @@
+"""The native argument marshalling (module _marshal) against the general way
+in Python: with the library's entry points replaced by recorders, both make
+the same call with the same arguments, over every form of argument that the
+native way takes; what it does not take it refuses without a call, and the
+binding then converts or rejects it as it always did.  (Device tensors need
+the GPU; the refusals of host tensors run on the CPU.)"""
+import ctypes
+
+import numpy as np
+import pytest
+
+import paper_1601_04033_amd as fa
+
+P = 1000
+i32, i64, f32, u64, sz, ptr = (ctypes.c_int32, ctypes.c_int64, ctypes.c_float, ctypes.c_uint64, ctypes.c_size_t,
+                               ctypes.c_void_p)
+S = "state"
+# argument kinds of the C ABI: a ctypes type, or ("array", type, index of its length's argument)
+SIGNATURES = {
+    "fasgd_apply_updates": [S, ("array", ptr, 4), ("array", i32, 4), ("array", i64, 4), i32, ptr],
+    "sasgd_apply_updates": [S, ("array", ptr, 4), ("array", i32, 4), ("array", i64, 4), i32, ptr],
+    "bfasgd_select_compact": [S, ptr, f32, f32, u64, i64, i32, ptr, ptr, i64, ptr, ptr, ptr, sz, ptr],
+    "bfasgd_select_compact_batch": [S, i32, ("array", ptr, 1), f32, f32, u64, ("array", i64, 1), ("array", i32, 1), ptr,
+                                    ptr, i64, ptr, ptr, ptr, sz, ptr],
+    "bfasgd_apply_sparse": [S, ptr, ptr, ptr, i64, i32, i64, ptr],
+    "fasgd_apply_with_push": [S, ptr, ptr, ptr, ptr, i64, i32, i64, ("array", ptr, 11), ("array", i32, 11),
+                              ("array", i64, 11), i32, ptr],
+    "fasgd_apply_with_push_and_select": [S, ptr, ptr, ptr, ptr, i64, i32, i64, ("array", ptr, 11), ("array", i32, 11),
+                                         ("array", i64, 11), i32, ptr, i32, f32, f32, u64, ptr, ptr, i64, ptr, ptr, ptr,
+                                         sz, ptr],
+    "fasgd_apply_pushes": [S, i32, ptr, ptr, ptr, ptr, i64, ("array", i32, 1), ("array", i64, 1), ptr],
+    "bfasgd_apply_cached": [S, ptr, ptr, ptr, ptr, i64, ptr, i32, i64, ptr],
+    "bfasgd_apply_fetch": [ptr, i64, ptr, ptr, ptr, ptr, i64, ptr],
+    "bfasgd_decide_segments": [S, ("array", i64, 2, 1), i32, f32, f32, u64, i64, i32, ptr, ptr, sz, ptr],
+    "bfasgd_apply_segments": [S, ptr, ("array", i64, 3, 1), i32, ptr, i32, i64, ptr],
+}
+
+
+class Recorder:
+    """A stand-in for the loaded library: every entry point records its arguments and returns `status`."""
+
+    def __init__(self):
+        self.calls, self.status, self._keep = [], 0, []
+        for name, kinds in SIGNATURES.items():
+            types = [k if not isinstance(k, (str, tuple)) else ptr for k in kinds]
+            setattr(self, name, ctypes.CFUNCTYPE(ctypes.c_int, *types)(self._record(name, kinds)))
+        lib = fa.load_library()
+        self.bfasgd_list_index_length = lib.bfasgd_list_index_length
+
+    def _record(self, name, kinds):
+        def f(*args):
+            seen = [name]
+            for k, x in zip(kinds, args):
+                if isinstance(k, tuple):
+                    n = args[k[2]] + (k[3] if len(k) > 3 else 0)
+                    seen.append(list(ctypes.cast(x, ctypes.POINTER(k[1]))[:n]))
+                else:
+                    seen.append(x)
+            self.calls.append(seen)
+            return self.status
+        return f
+
+    def fasgd_last_error(self):
+        return b"recorded"
+
+
+@pytest.fixture
+def recorder(monkeypatch):
+    native = fa._native()
+    rec = Recorder()
+    native.bind([ctypes.cast(getattr(rec, n), ptr).value for n in native.ENTRY_POINTS], fa._current_stream)
+    monkeypatch.setattr(fa, "load_library", lambda path=None: rec)
+    yield rec
+    monkeypatch.undo()
+    lib = fa.load_library()
+    native.bind([ctypes.cast(getattr(lib, n), ptr).value for n in native.ENTRY_POINTS], fa._current_stream)
+
+
+def test_every_marshalled_entry_point_is_declared():
+    assert set(fa._native().ENTRY_POINTS) == set(SIGNATURES) <= set(fa.ABI_FUNCTIONS)
+
+
+def things(dev):
+    import torch
+    t = {}
+    t["g"] = [torch.zeros(P, device=dev) for _ in range(64)]
+    t["idx"] = torch.zeros(P, device=dev, dtype=torch.int32)
+    t["val"] = torch.zeros(P, device=dev)
+    t["cnt"] = torch.zeros(1, device=dev, dtype=torch.int64)
+    t["seg"] = torch.zeros(5 + 3, device=dev, dtype=torch.int32)          # longer than needed: taken
+    t["ws"] = torch.zeros(4096, device=dev, dtype=torch.uint8)
+    t["bidx"] = torch.zeros(3, 70, device=dev, dtype=torch.int32)
+    t["bval"] = torch.zeros(3, 70, device=dev)
+    t["bcnt"] = torch.zeros(3, device=dev, dtype=torch.int64)
+    t["bseg"] = torch.zeros(3, 5, device=dev, dtype=torch.int32)
+    t["send"] = torch.zeros(2, device=dev, dtype=torch.uint8)
+    c = fa.fasgd_state()
+    c.P, c.lambda_, c.T = P, 8, 100
+    t["st"] = fa.State(c, {})
+    t["off"] = np.array([0, 400, P], dtype=np.int64)
+    return t
+
+
+def forms(t):
+    """(name, arguments, keywords) of calls in every plain form."""
+    st, g, idx, val, cnt, seg, ws = (t[k] for k in ("st", "g", "idx", "val", "cnt", "seg", "ws"))
+    out = []
+    for name in ("fasgd_apply_updates", "sasgd_apply_updates"):
+        for K in (1, 2, 31, 64):
+            out.append((name, (st, g[:K], [k % 8 for k in range(K)], [90 + k for k in range(K)]), {}))
+        out.append((name, (st, tuple(g[:2]), np.array([1, 2], np.int32), (3, np.int64(4))), {}))
+    for s in (None, seg):
+        out.append(("bfasgd_select_compact", (st, g[0], 5, 1e-8, 2 ** 63 + 5, 7, 3, idx, val, cnt, ws), {"seg_start": s}))
+        out.append(("bfasgd_apply_cached", (st, idx, val, cnt, g[2], 2, 9), {"seg_start": s}))
+        out.append(("bfasgd_apply_fetch", (g[0], idx, val, cnt), {"seg_start": s}))
+        out.append(("fasgd_apply_with_push_and_select",
+                    (st, idx, val, cnt, seg, 1, 2, g[:5], [0] * 5, range(5), g[6], 3, 2.5, 0.0, -1, idx, val, cnt, s, ws), {}))
+    for s in (None, t["bseg"]):
+        out.append(("bfasgd_select_compact_batch", (st, g[:3], 2.5, 0.25, 1, [5, 6, 7], [0, 1, 2], t["bidx"], t["bval"],
+                                                    t["bcnt"], ws), {"seg_start": s}))
+    out.append(("bfasgd_apply_sparse", (st, idx, val, cnt, np.int32(3), 50), {}))
+    out.append(("fasgd_apply_with_push", (st, idx, val, cnt, seg, 1, 2, g[:3], [0, 1, 2], [4, 5, 6]), {}))
+    out.append(("fasgd_apply_pushes", (st, t["bidx"], t["bval"], t["bcnt"], t["bseg"], [0, 1, 2], [4, 5, 6]), {}))
+    out.append(("bfasgd_decide_segments", (st, t["off"], 1.0, 1e-8, 3, 4, 5, t["send"], ws), {}))
+    out.append(("bfasgd_apply_segments", (st, g[0], t["off"], t["send"], 5, 6), {}))
+    return out
+
+
+def general(monkeypatch):
+    """The binding's general way alone."""
+    class Refuse:
+        def __getattr__(self, name):
+            return lambda *a: None
+    monkeypatch.setattr(fa, "_calls", Refuse())
+
+
+@pytest.mark.gpu
+def test_native_and_general_calls_are_the_same(recorder, monkeypatch):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    t = things(torch.device("cuda:0"))
+    side = torch.cuda.Stream()
+    taken = []
+
+    class Counting:
+        def __getattr__(self, name):
+            f = getattr(native, name)
+
+            def call(*a):
+                rc = f(*a)
+                taken.append((name, rc))
+                return rc
+            return call
+    native = fa._native()
+    calls = forms(t)
+    calls += [(n, a, dict(kw, stream=side)) for n, a, kw in calls]
+    calls += [("bfasgd_apply_sparse", (t["st"], t["idx"], torch.nn.Parameter(t["val"]), t["cnt"], 3, 50), {})]
+    for name, args, kw in calls:
+        with monkeypatch.context() as m:
+            m.setattr(fa, "_calls", Counting())
+            getattr(fa, name)(*args, **kw)
+        with monkeypatch.context() as m:
+            general(m)
+            getattr(fa, name)(*args, **kw)
+        assert taken and taken.pop() == (name, 0), name
+        assert len(recorder.calls) == 2 and recorder.calls[0] == recorder.calls[1], (name, kw, recorder.calls)
+        recorder.calls.clear()
+    with torch.cuda.stream(side):        # the current stream is looked up at each call
+        fa.bfasgd_apply_sparse(t["st"], t["idx"], t["val"], t["cnt"], 3, 50)
+    assert recorder.calls.pop()[-1] == side.cuda_stream
+    recorder.status = 2                  # the library's errors come through
+    with pytest.raises(fa.FasgdError, match="recorded"):
+        fa.bfasgd_apply_sparse(t["st"], t["idx"], t["val"], t["cnt"], 3, 50)
+
+
+def refusals(t, torch):
+    """(arguments of fasgd_apply_updates / bfasgd_apply_sparse / ..., the exception of the general way or None)."""
+    st, g, idx, val, cnt = t["st"], t["g"], t["idx"], t["val"], t["cnt"]
+
+    class Mine(torch.Tensor):
+        pass
+
+    mine = val.clone().as_subclass(Mine)
+    return [
+        ("fasgd_apply_updates", (st, [], [], []), ValueError),
+        ("fasgd_apply_updates", (st, g[:1] * 65, [0] * 65, [0] * 65), ValueError),
+        ("fasgd_apply_updates", (st, g[:2], [0], [0, 0]), ValueError),
+        ("fasgd_apply_updates", (st, g[:2], [0, 0], [0]), ValueError),
+        ("fasgd_apply_updates", (st, [g[0][:-1]], [0], [0]), ValueError),
+        ("fasgd_apply_updates", (st, [g[0].double()], [0], [0]), TypeError),
+        ("fasgd_apply_updates", (st, [None], [0], [0]), AttributeError),
+        ("fasgd_apply_updates", (st, g[:1], ["x"], [0]), ValueError),
+        ("bfasgd_apply_sparse", (st, idx, val[:-1], cnt, 0, 0), ValueError),
+        ("bfasgd_apply_sparse", (st, idx.long(), val, cnt, 0, 0), TypeError),
+        ("bfasgd_apply_sparse", (st, idx, val, cnt.int(), 0, 0), TypeError),
+        ("bfasgd_apply_sparse", (st, idx, torch.zeros(2 * P, device=val.device)[::2], cnt, 0, 0), TypeError),
+        ("bfasgd_apply_sparse", (st, idx, mine, cnt, 0, 0), None),
+        ("bfasgd_apply_sparse", (st, idx, val, cnt, 1.0, 2.5), None),
+        ("fasgd_apply_pushes", (st, t["bidx"], t["bval"][:2], t["bcnt"], t["bseg"], [0, 1, 2], [0, 0, 0]), ValueError),
+        ("fasgd_apply_pushes", (st, t["bidx"], t["bval"], t["bcnt"], t["bseg"][:, :4], [0, 1, 2], [0, 0, 0]), ValueError),
+        ("fasgd_apply_with_push", (st, idx, val, cnt, None, 1, 2, g[:1], [0], [0]), ValueError),
+        ("fasgd_apply_with_push", (st, idx, val, cnt, t["seg"][:4], 1, 2, g[:1], [0], [0]), ValueError),
+        ("bfasgd_apply_segments", (st, g[0], [0, 400, P], t["send"], 5, 6), None),
+        ("bfasgd_apply_segments", (st, g[0], t["off"].astype(np.int32), t["send"], 5, 6), None),
+        ("bfasgd_decide_segments", (st, t["off"], 1.0, 1e-8, 3, 4, 5, t["send"][:1], t["ws"]), ValueError),
+    ]
+
+
+@pytest.mark.gpu
+def test_what_is_not_plain_goes_the_general_way(recorder):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    t = things(torch.device("cuda:0"))
+    native = fa._native()
+    native_args = {"bfasgd_apply_sparse": lambda a: (a[0].c, *a[1:], None),
+                   "fasgd_apply_updates": lambda a: (a[0].c, *a[1:], None),
+                   "fasgd_apply_pushes": lambda a: (a[0].c, *a[1:], None),
+                   "fasgd_apply_with_push": lambda a: (a[0].c, *a[1:], None),
+                   "bfasgd_apply_segments": lambda a: (a[0].c, *a[1:], None),
+                   "bfasgd_decide_segments": lambda a: (a[0].c, *a[1:], None)}
+    for name, args, error in refusals(t, torch):
+        assert getattr(native, name)(*native_args[name](args)) is None, (name, args)
+        assert not recorder.calls, name
+        if error is None:
+            getattr(fa, name)(*args)
+            assert len(recorder.calls) == 1, name
+            recorder.calls.clear()
+        else:
+            with pytest.raises(error):
+                getattr(fa, name)(*args)
+            assert not recorder.calls, name
+
+
+def test_host_tensors_are_refused(recorder):
+    """Host tensors reach neither the library nor the current stream; the general way rejects them by name."""
+    import torch
+    t = things(torch.device("cpu"))
+    for name, args, kw in forms(t):
+        with pytest.raises(TypeError, match="must be a CUDA"):
+            getattr(fa, name)(*args, **kw)
+    assert not recorder.calls
+
+
+def test_wrong_arity_and_binding_are_errors():
+    native = fa._native()
+    with pytest.raises(TypeError):
+        native.fasgd_apply_updates(1, 2)
+    with pytest.raises(ValueError):
+        native.bind([0] * len(SIGNATURES), fa._current_stream)
+    with pytest.raises(ValueError):
+        native.bind([1], fa._current_stream)
