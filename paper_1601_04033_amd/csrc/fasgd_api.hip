@@ -839,6 +839,7 @@ fasgd_status bfasgd_apply_segments(fasgd_state* st, const float* grad, const int
     a.last_T = st->last_T;
     a.grad = grad;
     a.transmit = d_transmit;
+    a.P = st->P;
     a.coef = st->math_mode == FASGD_MATH_FAST ? st->alpha / tau_div : tau_div;
     a.last_T_value = static_cast<int32_t>(st->T);
     a.aligned = aligned(st->theta, 16) && aligned(st->n, 16) && aligned(st->b, 16) && aligned(st->v, 16) &&
@@ -846,7 +847,7 @@ fasgd_status bfasgd_apply_segments(fasgd_state* st, const float* grad, const int
     a.h = hyper_of(st);
     int64_t base = 0;
     for (int32_t g0 = 0; g0 < S; g0 += fasgd::kSegGroup) {
-        const fasgd::SegGroup g = segment_group(seg, S, g0, base);
+        fasgd::SegGroup g = segment_group(seg, S, g0, base);
         const hipError_t e = fasgd::launch_seg_apply(g, a, variant_of(st), stream);
         if (e != hipSuccess) return hip_fail(e, "bfasgd_apply_segments");
     }

@@ -178,7 +178,7 @@ struct PushBatchArgs {
 hipError_t launch_apply_pushes(const PushBatchArgs& a, int variant, bool aligned, hipStream_t s);
 
 // Paper-literal decisions per segment (groups of up to kSegGroup segments).
-constexpr int kSegGroup = 32;
+constexpr int kSegGroup = 128;
 
 struct SegGroup {
     int64_t start[kSegGroup + 1];          // offsets of the group's segments, start[n] = end of the last
@@ -197,6 +197,7 @@ struct SegApplyArgs {
     int32_t* last_T;
     const float* grad;
     const uint8_t* transmit;
+    int64_t P;
     float coef;             // as DenseArgs::coef for this push
     int32_t last_T_value;   // T
     int32_t aligned;        // every array 16-byte aligned
@@ -208,7 +209,8 @@ size_t segments_workspace_bytes(int64_t P, int32_t S);
 hipError_t launch_seg_decide(const SegGroup& g, const float* v, double* partial, float c, float eps_c,
                              uint64_t seed, uint32_t ctr_T, uint32_t ctr_client, uint8_t* transmit,
                              hipStream_t s);
-hipError_t launch_seg_apply(const SegGroup& g, const SegApplyArgs& a, int variant, hipStream_t s);
+// g.block_prefix is recounted in the apply's own blocks
+hipError_t launch_seg_apply(SegGroup& g, const SegApplyArgs& a, int variant, hipStream_t s);
 
 // dst[idx[i]] = val[i] for i < min(*d_count, capacity); indices outside
 // [0, P) are skipped.
