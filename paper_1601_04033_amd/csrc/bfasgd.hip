@@ -677,14 +677,29 @@ hipError_t launch_direct(const SelectArgs& a, const SelectBatch& bt, int B, bool
 }
 
 constexpr int kListBlock = 256;               // list kernels: 4 waves
-constexpr int kSparseE = 2;                   // list entries per lane
 constexpr int64_t kListMaxBlocks = 65536;     // grid cap of the list kernels (grid-stride)
 
 // A wave owns 64 E consecutive list entries and lane l takes entries
 // l, l + 64, ...: every gather instruction covers 64 consecutive entries
-// (ascending indices, so few cache lines), and each thread issues all
-// kSparseE of its gathers before the first update.
-template <int MODE>
+// (ascending indices, so few cache lines), and each thread issues all E of
+// its gathers before the first update.  Bound by whole-line traffic of the
+// state: at 10 % nearly every 128-byte line holds a listed parameter.
+// STREAM: the scattered stores (and the list's loads) are non-temporal, so
+// partly written lines leave the L2 caches at once instead of displacing
+// lines still to be read; lines that two waves share are then written twice,
+// which a longer run per wave (E = 6) makes rarer.  A whole push (selection
+// and this), plain E = 2 against STREAM with E = 2 and 6, same box:
+//   P, transmitted   plain    E = 2    E = 6
+//   1.8M, 20 %       22.1     22.5     25.0 us
+//   3.2M, 10 %       32.8     31.8     35.6
+//   5M, 10 %         54.5     46.9     47.0
+//   12M, 20 %        136      131      133
+//   25M, 10 %        276      258      243
+//   25M, 30 %        287      269      282
+//   300M, 10 %       3280     3090     2800
+//   300M, 2 %        1632     1566     1549
+// (non-temporal loads of the state cost 30 %: a line's second reader misses).
+template <int MODE, int E, bool STREAM>
 __global__ __launch_bounds__(kListBlock) void sparse_apply(const SparseArgs a)
 {
     int64_t m = *a.d_count;
@@ -693,28 +708,36 @@ __global__ __launch_bounds__(kListBlock) void sparse_apply(const SparseArgs a)
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t wave_id = (static_cast<int64_t>(blockIdx.x) * kListBlock + threadIdx.x) / kWave;
     const int64_t n_waves = static_cast<int64_t>(gridDim.x) * (kListBlock / kWave);
-    for (int64_t base = wave_id * kWave * kSparseE; base < m; base += n_waves * kWave * kSparseE) {
-        int64_t j[kSparseE];
-        float g[kSparseE], th[kSparseE], n[kSparseE], b[kSparseE], v[kSparseE];
+    for (int64_t base = wave_id * kWave * E; base < m; base += n_waves * kWave * E) {
+        int64_t j[E];
+        float g[E], th[E], n[E], b[E], v[E];
 #pragma unroll
-        for (int e = 0; e < kSparseE; ++e) {
+        for (int e = 0; e < E; ++e) {
             const int64_t i = base + e * kWave + lane;
             j[e] = -1;
             if (i < m) {
-                const int64_t x = a.idx[i];
-                if (x >= 0 && x < a.P) { j[e] = x; g[e] = a.val[i]; }
+                const int64_t x = STREAM ? __builtin_nontemporal_load(a.idx + i) : a.idx[i];
+                if (x >= 0 && x < a.P) { j[e] = x; g[e] = STREAM ? __builtin_nontemporal_load(a.val + i) : a.val[i]; }
             }
         }
 #pragma unroll
-        for (int e = 0; e < kSparseE; ++e) {
+        for (int e = 0; e < E; ++e) {
             if (j[e] >= 0) { th[e] = a.theta[j[e]]; n[e] = a.n[j[e]]; b[e] = a.b[j[e]]; v[e] = a.v[j[e]]; }
         }
 #pragma unroll
-        for (int e = 0; e < kSparseE; ++e) {
+        for (int e = 0; e < E; ++e) {
             if (j[e] >= 0) {
                 fasgd_step<MODE>(th[e], n[e], b[e], v[e], g[e], a.coef, h);
-                a.theta[j[e]] = th[e]; a.n[j[e]] = n[e]; a.b[j[e]] = b[e]; a.v[j[e]] = v[e];
-                a.last_T[j[e]] = a.last_T_value;
+                if (STREAM) {
+                    __builtin_nontemporal_store(th[e], a.theta + j[e]);
+                    __builtin_nontemporal_store(n[e], a.n + j[e]);
+                    __builtin_nontemporal_store(b[e], a.b + j[e]);
+                    __builtin_nontemporal_store(v[e], a.v + j[e]);
+                    __builtin_nontemporal_store(a.last_T_value, a.last_T + j[e]);
+                } else {
+                    a.theta[j[e]] = th[e]; a.n[j[e]] = n[e]; a.b[j[e]] = b[e]; a.v[j[e]] = v[e];
+                    a.last_T[j[e]] = a.last_T_value;
+                }
             }
         }
     }
@@ -815,19 +838,38 @@ hipError_t launch_select_after_mark(const SelectArgs& a, bool aligned, hipStream
     return hipGetLastError();
 }
 
-hipError_t launch_sparse(const SparseArgs& a, int variant, hipStream_t s)
+// Enough lanes for `capacity` entries (the count is only known on the
+// device); lanes past the count exit.
+template <int MODE, int E, bool STREAM>
+void launch_sparse_shape(const SparseArgs& a, hipStream_t s)
 {
-    // enough lanes for `capacity` entries (the count is only known on the
-    // device); lanes past the count exit
-    int64_t g = (a.capacity + int64_t(kListBlock) * kSparseE - 1) / (int64_t(kListBlock) * kSparseE);
+    int64_t g = (a.capacity + int64_t(kListBlock) * E - 1) / (int64_t(kListBlock) * E);
     if (g > kListMaxBlocks) g = kListMaxBlocks;
     if (g < 1) g = 1;
-    const unsigned grid = static_cast<unsigned>(g);
+    sparse_apply<MODE, E, STREAM><<<static_cast<unsigned>(g), kListBlock, 0, s>>>(a);
+}
+
+// By the size of the state (20 bytes per parameter): up to 3M parameters it
+// stays in the caches between pushes; beyond 16M it is larger than the 256 MB
+// Infinity Cache (see sparse_apply for both sides of each line).
+template <int MODE>
+void launch_sparse_variant(const SparseArgs& a, hipStream_t s)
+{
+    if (a.P <= 3'000'000)
+        launch_sparse_shape<MODE, 2, false>(a, s);
+    else if (a.P <= 16'000'000)
+        launch_sparse_shape<MODE, 2, true>(a, s);
+    else
+        launch_sparse_shape<MODE, 6, true>(a, s);
+}
+
+hipError_t launch_sparse(const SparseArgs& a, int variant, hipStream_t s)
+{
     switch (variant) {
-    case kernel_variant(MATH_FAST, 0): sparse_apply<kernel_variant(MATH_FAST, 0)><<<grid, kListBlock, 0, s>>>(a); break;
-    case kernel_variant(MATH_IEEE, 0): sparse_apply<kernel_variant(MATH_IEEE, 0)><<<grid, kListBlock, 0, s>>>(a); break;
-    case kernel_variant(MATH_FAST, 1): sparse_apply<kernel_variant(MATH_FAST, 1)><<<grid, kListBlock, 0, s>>>(a); break;
-    case kernel_variant(MATH_IEEE, 1): sparse_apply<kernel_variant(MATH_IEEE, 1)><<<grid, kListBlock, 0, s>>>(a); break;
+    case kernel_variant(MATH_FAST, 0): launch_sparse_variant<kernel_variant(MATH_FAST, 0)>(a, s); break;
+    case kernel_variant(MATH_IEEE, 0): launch_sparse_variant<kernel_variant(MATH_IEEE, 0)>(a, s); break;
+    case kernel_variant(MATH_FAST, 1): launch_sparse_variant<kernel_variant(MATH_FAST, 1)>(a, s); break;
+    case kernel_variant(MATH_IEEE, 1): launch_sparse_variant<kernel_variant(MATH_IEEE, 1)>(a, s); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
