@@ -743,6 +743,18 @@ __global__ __launch_bounds__(kListBlock) void sparse_apply(const SparseArgs a)
     }
 }
 
+// The list's values into a dense array, one partial 32-byte sector per entry;
+// a wave owns 64 E consecutive entries and loads them all first.  STREAM as
+// for sparse_apply.  Selection and copy together, plain E = 1 (the former
+// form), plain E = 2, STREAM with E = 2 and with E = 1, same box:
+//   P, transmitted   E = 1    E = 2    E = 2 s. E = 1 s.
+//   4M, 10 %         18.2     16.6     18.9     18.5 us
+//   8M, 5 %          27.1     23.9     26.8     26.2
+//   8M, 30 %         40.1     37.6     35.3     36.2
+//   20M, 20 %        86.2     81.9     77.7     80.2
+//   60M, 10 %        218      221      200      196
+//   60M, 30 %        242      257      235      226
+template <int E, bool STREAM>
 __global__ __launch_bounds__(kListBlock) void scatter_list(float* __restrict__ dst, int64_t P,
                                                        const int32_t* __restrict__ idx,
                                                        const float* __restrict__ val,
@@ -750,10 +762,30 @@ __global__ __launch_bounds__(kListBlock) void scatter_list(float* __restrict__ d
 {
     int64_t m = *d_count;
     if (m > capacity) m = capacity;
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * kListBlock;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * kListBlock + threadIdx.x; i < m; i += stride) {
-        const int64_t j = idx[i];
-        if (j >= 0 && j < P) dst[j] = val[i];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t wave_id = (static_cast<int64_t>(blockIdx.x) * kListBlock + threadIdx.x) / kWave;
+    const int64_t n_waves = static_cast<int64_t>(gridDim.x) * (kListBlock / kWave);
+    for (int64_t base = wave_id * kWave * E; base < m; base += n_waves * kWave * E) {
+        int64_t j[E];
+        float x[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int64_t i = base + e * kWave + lane;
+            j[e] = -1;
+            if (i < m) {
+                j[e] = STREAM ? __builtin_nontemporal_load(idx + i) : idx[i];
+                x[e] = STREAM ? __builtin_nontemporal_load(val + i) : val[i];
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            if (j[e] >= 0 && j[e] < P) {
+                if (STREAM)
+                    __builtin_nontemporal_store(x[e], dst + j[e]);
+                else
+                    dst[j[e]] = x[e];
+            }
+        }
     }
 }
 
@@ -875,13 +907,27 @@ hipError_t launch_sparse(const SparseArgs& a, int variant, hipStream_t s)
     return hipGetLastError();
 }
 
+template <int E, bool STREAM>
+void launch_scatter_shape(float* dst, int64_t P, const int32_t* idx, const float* val, const int64_t* d_count,
+                          int64_t capacity, hipStream_t s)
+{
+    int64_t g = (capacity + int64_t(kListBlock) * E - 1) / (int64_t(kListBlock) * E);
+    if (g > kListMaxBlocks) g = kListMaxBlocks;
+    if (g < 1) g = 1;
+    scatter_list<E, STREAM><<<static_cast<unsigned>(g), kListBlock, 0, s>>>(dst, P, idx, val, d_count, capacity);
+}
+
 hipError_t launch_scatter(float* dst, int64_t P, const int32_t* idx, const float* val,
                           const int64_t* d_count, int64_t capacity, hipStream_t s)
 {
-    int64_t g = (capacity + kListBlock - 1) / kListBlock;
-    if (g > kListMaxBlocks) g = kListMaxBlocks;
-    if (g < 1) g = 1;
-    scatter_list<<<static_cast<unsigned>(g), kListBlock, 0, s>>>(dst, P, idx, val, d_count, capacity);
+    // by the size of dst: up to 40 MB, about the L2 caches, and up to 160 MB,
+    // inside the Infinity Cache (see scatter_list for both sides of each line)
+    if (P <= 10'000'000)
+        launch_scatter_shape<2, false>(dst, P, idx, val, d_count, capacity, s);
+    else if (P <= 40'000'000)
+        launch_scatter_shape<2, true>(dst, P, idx, val, d_count, capacity, s);
+    else
+        launch_scatter_shape<1, true>(dst, P, idx, val, d_count, capacity, s);
     return hipGetLastError();
 }
 

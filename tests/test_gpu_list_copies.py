@@ -1,0 +1,39 @@
+"""GPU: the list copies (a client's refresh, scattered and by segments) on both
+sides of each change of form and at the edges of a block, a wave's run and the
+64 entries that a segment loads ahead, against torch's index assignment."""
+import pytest
+
+import paper_1601_04033_amd as fa
+from helpers import gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("P", [1, 255, 256, 257, 2047, 2048, 2049, 4099, 10_000_000, 10_000_001, 40_000_000, 40_000_001])
+@pytest.mark.parametrize("density", [0.0, 0.01, 0.25, 1.0])
+def test_list_copies(P, density):
+    import torch
+    dev = gpu()
+    gen = torch.Generator(device=dev).manual_seed(P)
+    copy = torch.randn(P, device=dev, generator=gen)
+    listed = torch.nonzero(torch.rand(P, device=dev, generator=gen) < density).reshape(-1)
+    m = listed.numel()
+    idx = torch.cat([listed.int(), torch.zeros(3, device=dev, dtype=torch.int32)])   # entries past the count
+    val = torch.randn(m + 3, device=dev, generator=gen)
+    cnt = torch.full((1,), m, device=dev, dtype=torch.int64)
+    edges = torch.arange(fa.bfasgd_list_index_length(P), device=dev) * 256
+    seg = torch.searchsorted(listed, edges.clamp_(max=P)).int()
+    want = copy.clone()
+    want[listed] = val[:m]
+    for index in (None, seg):
+        got = copy.clone()
+        fa.bfasgd_apply_fetch(got, idx, val, cnt, seg_start=index)
+        assert torch.equal(got, want), (P, density, index is not None)
+    if m > 1:                                    # the capacity cuts the list
+        cut = m // 2
+        want = copy.clone()
+        want[listed[:cut]] = val[:cut]
+        for index in (None, seg):
+            got = copy.clone()
+            fa.bfasgd_apply_fetch(got, idx[:cut].contiguous(), val[:cut].contiguous(), cnt, seg_start=index)
+            assert torch.equal(got, want), (P, density, index is not None, "cut")
