@@ -38,8 +38,8 @@ constexpr int kBatch = 8;          // their gradients loaded together before use
 // 25M parameters (77 % against 70 % of 8 TB/s) and 26.9 against 28.9 ms at
 // 1e9; at K = 8, 80 % against 73 %.  The FASGD pass loads its gradients
 // kLaneBatch at a time (25 VGPRs, 8 waves per SIMD, the most a SIMD holds;
-// batches of 2, 4, 6 measured 2-7 % slower) in blocks of kLaneBlock threads
-// (128 and 512: 2-5 % slower).  The pass with a push, SASGD and synchronous
+// batches of 2, 4, 6 measured 2-7 % slower; up to 2M parameters lane_batch)
+// in blocks of kLaneBlock threads (128 and 512: 2-5 % slower).  The pass with a push, SASGD and synchronous
 // SGD take 4 at a time (measured best for each; SASGD 0.52 against 0.56 ms
 // at 25M).
 constexpr int kLaneBlock = 256;
@@ -49,6 +49,12 @@ constexpr int kSgdBatch = 4;       // SASGD and synchronous SGD
 constexpr int kIeeeBatch = 4;      // the IEEE passes in the short sequences (short_updates)
 static_assert(kIeeeBatch == kPushBatch, "the pass with a push hands its first batch to short_updates");
 
+// The FASGD pass of up to 2M parameters has few waves per SIMD and takes more
+// gradients at a time: up to 500k 8, then 4.  Batches of 3, 4 and 8, same box:
+// 300k, K = 8 5.6, 5.1, 5.2 us; 300k, K = 32 12.1, 11.1, 10.3; 700k, K = 32
+// 22.9, 21.6, 21.1; 1M, K = 24 22.9, 22.9, 23.4; 1.8M, K = 16 31.5, 30.4, 30.8;
+// 2.5M, K = 24 54.3, 55.1, 55.2.
+constexpr int lane_batch(int64_t P) { return P <= 500'000 ? 8 : P <= 2'000'000 ? 4 : kLaneBatch; }
 unsigned lane_grid(int64_t P) { return static_cast<unsigned>((P + kLaneBlock - 1) / kLaneBlock); }
 
 __device__ __forceinline__ f4 ld4(const float* p)
@@ -84,6 +90,19 @@ __device__ __forceinline__ void pass_step(float& th, float& n, float& b, float& 
         fasgd_step_short<MODE>(th, n, b, v, g, coef, h);
     else
         fasgd_step<MODE>(th, n, b, v, g, coef, h);
+}
+
+// The gradients from k on (fewer than a batch) at parameter j, every load
+// before the first use: one at a time, each waited for the one before it
+// (25M parameters, K = 2: 169 -> 155 us; K = 8: 246 -> 241; 12M, K = 5:
+// 100 -> 97; SASGD at 25M, K = 3: 113 -> 89).  Not in the pass with a push,
+// where it lost (the 25M step with K = 2 197 -> 213 us, with K = 5 245 -> 257).
+template <int N>
+__device__ __forceinline__ void load_rest(const DenseArgs& a, int64_t j, int k, float (&g)[N])
+{
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+        if (k + u < a.K) g[u] = ldnt(a.grad[k + u] + j);
 }
 
 unsigned grid_for(int64_t items)
@@ -487,7 +506,8 @@ __device__ __forceinline__ bool short_pass(float v, const Hyper& h)
 // and divisor checks this replaced, 760 us with the new ones in batches of 3
 // (4: 717, 6: 711, 8: 718), 668 us with the next batch of 4 loaded ahead
 // (2: 721, 3: 679, 6: 674); the FAST pass takes 645 us.
-template <int MODE>
+// REST: the gradients after the last whole batch by load_rest.
+template <int MODE, bool REST>
 __device__ __forceinline__ void short_updates(const DenseArgs& a, int64_t j, const float (&g0)[kIeeeBatch], float& th,
                                               float& n, float& b, float& v)
 {
@@ -508,9 +528,16 @@ __device__ __forceinline__ void short_updates(const DenseArgs& a, int64_t j, con
 #pragma unroll
             for (int u = 0; u < kIeeeBatch; ++u) g[u] = next[u];
         }
+        float rest[kIeeeBatch - 1];
+        if (REST) load_rest(a, j, k + kIeeeBatch, rest);
 #pragma unroll
         for (int u = 0; u < kIeeeBatch; ++u) fasgd_step_short<MODE>(th, n, b, v, g[u], a.coef[k + u], h);
-        for (k += kIeeeBatch; k < K; ++k) fasgd_step_short<MODE>(th, n, b, v, ldnt(a.grad[k] + j), a.coef[k], h);
+        k += kIeeeBatch;
+#pragma unroll
+        for (int u = 0; u < kIeeeBatch - 1; ++u)
+            if (REST && k + u < K) fasgd_step_short<MODE>(th, n, b, v, rest[u], a.coef[k + u], h);
+        if (!REST)
+            for (; k < K; ++k) fasgd_step_short<MODE>(th, n, b, v, ldnt(a.grad[k] + j), a.coef[k], h);
     }
 }
 
@@ -525,7 +552,7 @@ __device__ __forceinline__ void push_updates(const DenseArgs& a, const PushArgs&
     const int K = a.K;
     if (listed) pass_step<MODE, SHORT>(th, n, b, v, push_g, p.coef, h);
     if (SHORT && k0 == kPushBatch) {
-        short_updates<MODE>(a, jl, g0, th, n, b, v);
+        short_updates<MODE, false>(a, jl, g0, th, n, b, v);
         return;
     }
 #pragma unroll
@@ -668,7 +695,7 @@ __global__ __launch_bounds__(kLaneBlock) void fasgd_cached_push_lane(const Dense
     stnt(a.v + j, v);
 }
 
-template <int MODE, bool SHORT>
+template <int MODE, int BATCH, bool SHORT>
 __device__ __forceinline__ void lane_updates(const DenseArgs& a, int64_t j, float& th, float& n, float& b, float& v)
 {
     const Hyper h = a.h;
@@ -678,35 +705,39 @@ __device__ __forceinline__ void lane_updates(const DenseArgs& a, int64_t j, floa
         float g[kIeeeBatch];
 #pragma unroll
         for (int u = 0; u < kIeeeBatch; ++u) g[u] = ldnt(a.grad[u] + j);
-        short_updates<MODE>(a, j, g, th, n, b, v);
+        short_updates<MODE, true>(a, j, g, th, n, b, v);
         return;
     }
-    for (; k + kLaneBatch <= K; k += kLaneBatch) {
-        float g[kLaneBatch];
+    for (; k + BATCH <= K; k += BATCH) {
+        float g[BATCH];
 #pragma unroll
-        for (int u = 0; u < kLaneBatch; ++u) g[u] = ldnt(a.grad[k + u] + j);
+        for (int u = 0; u < BATCH; ++u) g[u] = ldnt(a.grad[k + u] + j);
 #pragma unroll
-        for (int u = 0; u < kLaneBatch; ++u) pass_step<MODE, SHORT>(th, n, b, v, g[u], a.coef[k + u], h);
+        for (int u = 0; u < BATCH; ++u) pass_step<MODE, SHORT>(th, n, b, v, g[u], a.coef[k + u], h);
     }
-    for (; k < K; ++k) pass_step<MODE, SHORT>(th, n, b, v, ldnt(a.grad[k] + j), a.coef[k], h);
+    float g[BATCH - 1];
+    load_rest(a, j, k, g);
+#pragma unroll
+    for (int u = 0; u < BATCH - 1; ++u)
+        if (k + u < K) pass_step<MODE, SHORT>(th, n, b, v, g[u], a.coef[k + u], h);
 }
 
 // K-fused FASGD, one parameter per thread (any 4-byte alignment): the pass
 // for every P below kMaxScalarItems.
-template <int MODE>
+template <int MODE, int BATCH>
 __global__ __launch_bounds__(kLaneBlock) void fasgd_dense_lane(const DenseArgs a)
 {
     const int64_t j = static_cast<int64_t>(blockIdx.x) * kLaneBlock + threadIdx.x;
     if (j >= a.P) return;
     float th = ldnt(a.theta + j), n = ldnt(a.n + j), b = ldnt(a.b + j), v = ldnt(a.v + j);
     if (short_pass<MODE>(v, a.h)) {
-        lane_updates<MODE, true>(a, j, th, n, b, v);
+        lane_updates<MODE, BATCH, true>(a, j, th, n, b, v);
         if (__builtin_expect(__ballot(v != v) != 0, 0)) {   // an infinite or NaN x: the pass again, divisor by divisor
             th = a.theta[j]; n = a.n[j]; b = a.b[j]; v = a.v[j];
-            lane_updates<MODE, false>(a, j, th, n, b, v);
+            lane_updates<MODE, BATCH, false>(a, j, th, n, b, v);
         }
     } else {
-        lane_updates<MODE, false>(a, j, th, n, b, v);
+        lane_updates<MODE, BATCH, false>(a, j, th, n, b, v);
     }
     stnt(a.theta + j, th);
     stnt(a.n + j, n);
@@ -770,10 +801,11 @@ __global__ __launch_bounds__(kLaneBlock) void sgd_dense_lane(const DenseArgs a)
 #pragma unroll
         for (int u = 0; u < kSgdBatch; ++u) th = fmaf(-a.coef[k + u], SYNC ? g[u] / lam : g[u], th);
     }
-    for (; k < K; ++k) {
-        const float g = ldnt(a.grad[k] + j);
-        th = fmaf(-a.coef[k], SYNC ? g / lam : g, th);
-    }
+    float g[kSgdBatch - 1];
+    load_rest(a, j, k, g);
+#pragma unroll
+    for (int u = 0; u < kSgdBatch - 1; ++u)
+        if (k + u < K) th = fmaf(-a.coef[k + u], SYNC ? g[u] / lam : g[u], th);
     stnt(a.theta + j, th);
 }
 
@@ -844,10 +876,15 @@ PushArgs readable_list(const PushArgs& p)
 template <int VARIANT>
 void launch_dense_variant(const DenseArgs& a, hipStream_t s)
 {
-    if (a.P <= kMaxScalarItems)
-        fasgd_dense_lane<VARIANT><<<lane_grid(a.P), kLaneBlock, 0, s>>>(a);
-    else
+    if (a.P <= kMaxScalarItems) {
+        switch (lane_batch(a.P)) {
+        case 8: fasgd_dense_lane<VARIANT, 8><<<lane_grid(a.P), kLaneBlock, 0, s>>>(a); break;
+        case 4: fasgd_dense_lane<VARIANT, 4><<<lane_grid(a.P), kLaneBlock, 0, s>>>(a); break;
+        default: fasgd_dense_lane<VARIANT, kLaneBatch><<<lane_grid(a.P), kLaneBlock, 0, s>>>(a);
+        }
+    } else {
         fasgd_dense_vec<VARIANT><<<grid_for((a.P >> 2) + 1), kBlock, 0, s>>>(a);
+    }
 }
 
 template <int VARIANT>
