@@ -78,11 +78,10 @@ __device__ __forceinline__ int64_t wave_tile()
     return static_cast<int64_t>(blockIdx.x) * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
 }
 
-// The arguments of push blockIdx.y of a batch: its gradient, counter words,
-// list, count, list index and workspace slice.
-__device__ __forceinline__ SelectArgs push_args(const SelectArgs& a0, const SelectBatch& bt)
+// The arguments of push b of a batch: its gradient, counter words, list,
+// count, list index and workspace slice.
+__device__ __forceinline__ SelectArgs push_args(const SelectArgs& a0, const SelectBatch& bt, int b)
 {
-    const int b = blockIdx.y;
     if (b == 0) return a0;
     SelectArgs a = a0;
     a.grad = bt.grad[b];
@@ -152,9 +151,151 @@ __device__ __forceinline__ uint32_t mark_tile(const SelectArgs& a, int64_t tile,
     return count;
 }
 
+// Several pushes decided from one v: a wave marks its tile for pushes
+// [b0, b0 + nb), so v is read once for all of them and both sides of the
+// transmit test are formed once.  The tile must be full and aligned and its
+// global chunk indexes must share their high word (shared_tile); the counts
+// go to the pushes' tile counts (STORE_COUNT) or to s_cnt[(b - b0) * stride].
+// Per push the bits are mark_tile's.
+__device__ __forceinline__ bool shared_tile(const SelectArgs& a, int64_t tile, bool aligned)
+{
+    const uint32_t q_lo = static_cast<uint32_t>(a.chunk_base + static_cast<uint64_t>(tile * kChunksPerTile));
+    return aligned && (tile + 1) * kChunksPerTile * 4 <= a.P && q_lo <= 0xffffffffu - (kChunksPerTile - 1);
+}
+
+template <bool STORE_COUNT>
+__device__ __forceinline__ void mark_tile_shared(const SelectArgs& a, const SelectBatch& bt, int b0, int nb,
+                                                 int64_t tile, int lane, uint32_t* s_cnt, int stride)
+{
+    const int64_t q0 = tile * kChunksPerTile + lane;
+    f4 v[kTileSegs];
+    float t[kTileSegs][4], u[kTileSegs][4];
+#pragma unroll
+    for (int s = 0; s < kTileSegs; ++s) v[s] = *reinterpret_cast<const f4*>(a.v + (q0 + s * kWave) * 4);
+#pragma unroll
+    for (int s = 0; s < kTileSegs; ++s)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) transmit_sides(v[s][k], a.c, a.eps_c, t[s][k], u[s][k]);
+    const uint64_t qg = a.chunk_base + static_cast<uint64_t>(tile * kChunksPerTile);   // wave-uniform
+    const uint32_t q_hi = static_cast<uint32_t>(qg >> 32);
+    const uint32_t q_lo = static_cast<uint32_t>(qg) + static_cast<uint32_t>(lane);
+    for (int g = 0; g < nb; ++g) {
+        const int b = b0 + g;
+        int word_lo = 0, word_hi = 0;   // as in mark_tile
+        uint32_t count = 0;
+#pragma unroll
+        for (int s = 0; s < kTileSegs; ++s) {
+            const uint4 w = philox4x32_10(make_uint4(q_lo + s * kWave, q_hi, bt.ctr_T[b], bt.ctr_client[b]), a.key0,
+                                          a.key1);
+            const uint32_t word[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint64_t bk = __builtin_amdgcn_ballot_w64(transmit_test(word[k], t[s][k], u[s][k]));
+                count += static_cast<uint32_t>(__popcll(bk));
+                word_lo = amdgcn_writelane(static_cast<int>(bk), 4 * s + k, word_lo);
+                word_hi = amdgcn_writelane(static_cast<int>(bk >> 32), 4 * s + k, word_hi);
+            }
+        }
+        const size_t off = b * bt.ws_stride;
+        uint64_t* ballots = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(a.ballots) + off);
+        if (lane < kTileWords)
+            ballots[tile * kTileWords + lane] =
+                (static_cast<uint64_t>(static_cast<uint32_t>(word_hi)) << 32) | static_cast<uint32_t>(word_lo);
+        if (lane == 0) {
+            if (STORE_COUNT)
+                reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(a.tile_count) + off)[tile] = count;
+            else
+                s_cnt[g * stride] = count;
+        }
+    }
+}
+
+// Mark one segment, with bounds, and return its transmit count: the tiles
+// that are not shared_tile (rolled, so that they cost the kernels no
+// registers).
+__device__ __forceinline__ uint32_t mark_segment(const SelectArgs& a, int64_t seg, int lane)
+{
+    const int64_t q = seg * kWave + lane;
+    uint32_t nib = 0;
+    if (q < n_chunks(a.P)) {
+        const f4 v = load_chunk(a.v, q, a.P);
+        const uint64_t qg = a.chunk_base + static_cast<uint64_t>(q);
+        const uint4 w = philox4x32_10(
+            make_uint4(static_cast<uint32_t>(qg), static_cast<uint32_t>(qg >> 32), a.ctr_T, a.ctr_client), a.key0,
+            a.key1);
+        nib = transmit_bit(w.x, v[0], a.c, a.eps_c) | (transmit_bit(w.y, v[1], a.c, a.eps_c) << 1) |
+              (transmit_bit(w.z, v[2], a.c, a.eps_c) << 2) | (transmit_bit(w.w, v[3], a.c, a.eps_c) << 3);
+    }
+    uint32_t count = 0;
+    uint64_t mine = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint64_t bk = __builtin_amdgcn_ballot_w64(((nib >> k) & 1u) != 0);
+        count += static_cast<uint32_t>(__popcll(bk));
+        if (lane == k) mine = bk;
+    }
+    if (lane < 4) a.ballots[seg * 4 + lane] = mine;
+    return count;
+}
+
+// One tile for pushes [b0, b0 + nb) of a batch.
+template <bool STORE_COUNT>
+__device__ __forceinline__ void mark_pushes(const SelectArgs& a0, const SelectBatch& bt, int b0, int nb, int64_t tile,
+                                            int lane, bool aligned, uint32_t* s_cnt, int stride)
+{
+    if (shared_tile(a0, tile, aligned)) {
+        mark_tile_shared<STORE_COUNT>(a0, bt, b0, nb, tile, lane, s_cnt, stride);
+        return;
+    }
+#pragma clang loop unroll(disable)
+    for (int g = 0; g < nb; ++g) {
+        const SelectArgs a = push_args(a0, bt, b0 + g);
+        uint32_t count = 0;
+#pragma clang loop unroll(disable)
+        for (int s = 0; s < kTileSegs; ++s) count += mark_segment(a, tile * kTileSegs + s, lane);
+        if (lane == 0) {
+            if (STORE_COUNT)
+                a.tile_count[tile] = count;
+            else
+                s_cnt[g * stride] = count;
+        }
+    }
+}
+
+// Pushes a wave marks together (the grid's y index counts such groups).  From
+// 4M parameters on, where v and the gradients no longer share the caches
+// (the saved reads of v are HBM traffic); below, the vector ALU bounds the
+// mark and fewer, longer waves balance worse.  Selection and apply of B
+// pushes, one at a time against groups of 2, 4 and 8, same box:
+//   P, B, transmitted    1       2       4       8
+//   1.8M, 16, 20 %      75.7    75.3    76.9    80.0 us
+//   3M, 3, 20 %         44.1    43.7    44.6    44.5
+//   3M, 16, 20 %        123     120     118     120
+//   6M, 2, 10 %         64.3    62.4    62.4    62.0
+//   6M, 8, 10 %         126     123     121     123
+//   12M, 32, 10 %       725     693     678     672
+//   39M, 8, 10 %        791     755     744     745
+constexpr int kMarkPushes = 4;
+constexpr int64_t kMarkSharedFrom = 4'000'000;
+int mark_group(int64_t P, int B, bool aligned)
+{
+    return aligned && P >= kMarkSharedFrom ? (B < kMarkPushes ? B : kMarkPushes) : 1;
+}
+
+__global__ __launch_bounds__(kSelBlock) void select_mark_shared(const SelectArgs a0, const SelectBatch bt, int B, int G)
+{
+    const int b0 = blockIdx.y * G;
+    const int nb = B - b0 < G ? B - b0 : G;
+    if (blockIdx.x == 0 && static_cast<int>(threadIdx.x) < nb)   // for the scan launch
+        *push_args(a0, bt, b0 + threadIdx.x).groups_done = 0u;
+    const int64_t tile = wave_tile();
+    if (tile >= a0.n_tiles) return;
+    mark_pushes<true>(a0, bt, b0, nb, tile, threadIdx.x & (kWave - 1), true, nullptr, 0);
+}
+
 __global__ __launch_bounds__(kSelBlock) void select_mark(const SelectArgs a0, const SelectBatch bt, bool aligned)
 {
-    const SelectArgs a = push_args(a0, bt);
+    const SelectArgs a = push_args(a0, bt, blockIdx.y);
     if (blockIdx.x == 0 && threadIdx.x == 0) *a.groups_done = 0u;   // for the scan launch
     const int64_t tile = wave_tile();
     if (tile >= a.n_tiles) return;
@@ -262,7 +403,7 @@ __device__ __forceinline__ uint32_t wave_tile_bits(const SelectArgs& a, int64_t 
 template <bool FUSED_TOP, bool FROM_BALLOTS>
 __global__ __launch_bounds__(kScanBlock) void select_scan(const SelectArgs a0, const SelectBatch bt)
 {
-    const SelectArgs a = push_args(a0, bt);
+    const SelectArgs a = push_args(a0, bt, blockIdx.y);
     const int64_t t = static_cast<int64_t>(blockIdx.x) * kScanBlock + threadIdx.x;
     uint32_t c = 0;
     if (FROM_BALLOTS) {
@@ -292,7 +433,7 @@ __global__ __launch_bounds__(kScanBlock) void select_scan(const SelectArgs a0, c
 
 __global__ __launch_bounds__(kScanBlock) void select_top(const SelectArgs a0, const SelectBatch bt)
 {
-    const SelectArgs a = push_args(a0, bt);
+    const SelectArgs a = push_args(a0, bt, blockIdx.y);
     scan_groups(a, (a.n_tiles + kScanBlock - 1) / kScanBlock, false);
 }
 
@@ -441,7 +582,7 @@ template <bool EARLY>
 __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void select_scatter(
     const SelectArgs a0, const SelectBatch bt, bool aligned)
 {
-    const SelectArgs a = push_args(a0, bt);
+    const SelectArgs a = push_args(a0, bt, blockIdx.y);
     __shared__ int32_t s_idx[kWavesPerBlock][kStageEntries];
     __shared__ float s_val[kWavesPerBlock][kStageEntries];
     const int64_t tile = wave_tile();
@@ -487,7 +628,7 @@ __global__ __launch_bounds__(TPB * kWave) void select_mark_totals(const SelectAr
                                                                   bool aligned)
 {
     static_assert(TPB * kChunksPerTile * 4 < 65536 && TPB <= kWave, "a block total fits 16 bits");
-    const SelectArgs a = push_args(a0, bt);
+    const SelectArgs a = push_args(a0, bt, blockIdx.y);
     __shared__ uint32_t s_cnt[TPB];
     __shared__ uint32_t s_arrived;
     if (threadIdx.x == 0) s_arrived = 0;
@@ -514,6 +655,42 @@ __global__ __launch_bounds__(TPB * kWave) void select_mark_totals(const SelectAr
         const uint32_t inc = wave_inclusive_scan(c);
         if (lane < TPB && t0 + lane < a.n_tiles) a.tile_offset[t0 + lane] = inc - c;
         if (lane == TPB - 1) reinterpret_cast<uint16_t*>(a.group_total)[blockIdx.x] = static_cast<uint16_t>(inc);
+    }
+}
+
+// The same for pushes [G blockIdx.y, G blockIdx.y + G) of a batch of B
+// (16-byte aligned arrays), marked together.
+template <int TPB>
+__global__ __launch_bounds__(TPB * kWave) void select_mark_totals_shared(const SelectArgs a0, const SelectBatch bt,
+                                                                         int B, int G)
+{
+    __shared__ uint32_t s_cnt[kMarkPushes][TPB];
+    __shared__ uint32_t s_arrived;
+    if (threadIdx.x == 0) s_arrived = 0;
+    __syncthreads();
+    const int b0 = blockIdx.y * G;
+    const int nb = B - b0 < G ? B - b0 : G;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t t0 = static_cast<int64_t>(blockIdx.x) * TPB;
+    const int64_t tile = t0 + w;
+    const int lane = threadIdx.x & (kWave - 1);
+    if (tile < a0.n_tiles)
+        mark_pushes<false>(a0, bt, b0, nb, tile, lane, true, &s_cnt[0][w], TPB);
+    else if (lane == 0)
+        for (int g = 0; g < nb; ++g) s_cnt[g][w] = 0;
+    int last = 0;
+    if (lane == 0)   // release / acquire, after this lane's counts: the last wave to arrive sees every count
+        last = __hip_atomic_fetch_add(&s_arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP) == TPB - 1;
+    if (__builtin_amdgcn_readfirstlane(last)) {
+        for (int g = 0; g < nb; ++g) {
+            const size_t off = (b0 + g) * bt.ws_stride;
+            uint32_t* tile_offset = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(a0.tile_offset) + off);
+            uint16_t* totals = reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(a0.group_total) + off);
+            const uint32_t c = lane < TPB ? s_cnt[g][lane] : 0u;
+            const uint32_t inc = wave_inclusive_scan(c);
+            if (lane < TPB && t0 + lane < a0.n_tiles) tile_offset[t0 + lane] = inc - c;
+            if (lane == TPB - 1) totals[blockIdx.x] = static_cast<uint16_t>(inc);
+        }
     }
 }
 
@@ -609,7 +786,7 @@ template <int TPB, int KT>
 __global__ __launch_bounds__(kSelBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void select_scatter_direct(
     const SelectArgs a0, const SelectBatch bt, bool aligned)
 {
-    const SelectArgs a = push_args(a0, bt);
+    const SelectArgs a = push_args(a0, bt, blockIdx.y);
     __shared__ int32_t s_idx[kWavesPerBlock][kStageEntries];
     __shared__ float s_val[kWavesPerBlock][kStageEntries];
     const int64_t tile = wave_tile();
@@ -658,8 +835,12 @@ hipError_t launch_direct(const SelectArgs& a, const SelectBatch& bt, int B, bool
         select_count_totals<TPB><<<static_cast<unsigned>((a.n_tiles + kSelBlock - 1) / kSelBlock), kSelBlock, 0,
                                    s>>>(a);
     } else {
-        const dim3 mgrid(static_cast<unsigned>(blocks), static_cast<unsigned>(B));
-        select_mark_totals<TPB><<<mgrid, TPB * kWave, 0, s>>>(a, bt, aligned);
+        const int G = mark_group(a.P, B, aligned);
+        const dim3 mgrid(static_cast<unsigned>(blocks), static_cast<unsigned>((B + G - 1) / G));
+        if (G > 1)
+            select_mark_totals_shared<TPB><<<mgrid, TPB * kWave, 0, s>>>(a, bt, B, G);
+        else
+            select_mark_totals<TPB><<<mgrid, TPB * kWave, 0, s>>>(a, bt, aligned);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -823,7 +1004,11 @@ hipError_t launch_select(const SelectArgs& a, const SelectBatch& bt, int B, bool
     if (a.n_tiles <= kDirectMaxTiles) return launch_direct<16>(a, bt, B, aligned, false, s);
     hipError_t e;
     const dim3 grid(gx, static_cast<unsigned>(B));
-    select_mark<<<grid, kSelBlock, 0, s>>>(a, bt, aligned);
+    const int G = mark_group(a.P, B, aligned);
+    if (G > 1)
+        select_mark_shared<<<dim3(gx, static_cast<unsigned>((B + G - 1) / G)), kSelBlock, 0, s>>>(a, bt, B, G);
+    else
+        select_mark<<<grid, kSelBlock, 0, s>>>(a, bt, aligned);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (groups <= static_cast<unsigned>(kFusedTopGroups)) {

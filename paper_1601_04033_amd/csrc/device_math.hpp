@@ -181,13 +181,23 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 x, uint32_t k0, uint32_t k1
 // division-free form r (t + c) < t with t = v + eps_c: both sums are fp32
 // and the fused multiply-add rounds once, so the sign of r*u - t is exact.
 // r is the top 24 bits of a Philox word scaled into [0, 1).
-__device__ __forceinline__ uint32_t transmit_bit(uint32_t word, float v, float c, float eps_c)
+__device__ __forceinline__ void transmit_sides(float v, float c, float eps_c, float& t, float& u)
+{
+#pragma clang fp contract(off)
+    t = v + eps_c;
+    u = t + c;
+}
+__device__ __forceinline__ bool transmit_test(uint32_t word, float t, float u)
 {
 #pragma clang fp contract(off)
     const float r = static_cast<float>(word >> 8) * 0x1p-24f;
-    const float t = v + eps_c;
-    const float u = t + c;
-    return fmaf(r, u, -t) < 0.0f ? 1u : 0u;
+    return fmaf(r, u, -t) < 0.0f;
+}
+__device__ __forceinline__ uint32_t transmit_bit(uint32_t word, float v, float c, float eps_c)
+{
+    float t, u;
+    transmit_sides(v, c, eps_c, t, u);
+    return transmit_test(word, t, u) ? 1u : 0u;
 }
 
 }  // namespace fasgd
