@@ -4,22 +4,21 @@
 // Work is cut into wave tiles of kTileSegs segments of 64 chunks (one chunk is
 // 4 consecutive parameters, one 16-byte vector).  Every wave owns one tile and
 // never waits on another wave, so no launch has a block barrier in its
-// streaming part.  Selection runs in three or four launches (calls of up to
-// about 50M parameters: two, described at select_mark_totals):
+// streaming part.  Selection runs in three launches (calls of up to about 50M
+// parameters: two, described at select_mark_totals):
 //   mark     the wave loads its tile of v, draws one Philox4x32-10 call per
 //            chunk (the counter is the global chunk index, so one call feeds
 //            one vector of v), forms four ballots per segment (1 bit per
 //            parameter), stores the tile's ballot words in one store and its
 //            transmit count;
 //   scan     one block per 1024 tiles scans their counts (offsets within the
-//            group) and records the group total; the group totals are
-//            scanned and the device count written by the last scan block to
-//            finish or, for many groups, by one more single-block launch;
-//   scatter  the wave loads its tile of gradients, reads its ballot words
-//            (scalar loads), places every transmitted (index, value) pair in
-//            an LDS stage at the popcount of the bits before it (ascending
-//            index order), and writes the staged run at group offset + tile
-//            offset in contiguous stores.
+//            group) and records the group total;
+//   scatter  the wave sums the totals of the groups before its own, loads its
+//            tile of gradients, reads its ballot words (scalar loads), places
+//            every transmitted (index, value) pair in an LDS stage at the
+//            popcount of the bits before it (ascending index order), and
+//            writes the staged run at group position + tile offset in
+//            contiguous stores.
 // When the mark step ran inside the preceding dense pass (which leaves the
 // ballot words but no tile counts), the scan counts each tile's ballot bits
 // (in the two-launch range, a count launch does, for the direct scatter).
@@ -50,7 +49,7 @@ constexpr int kTileWords = 4 * kTileSegs;     // ballot words per tile
 constexpr int64_t kChunksPerTile = int64_t(kTileSegs) * kWave;  // 256 chunks = 1024 parameters
 constexpr int kScanBlock = 1024;              // tiles per scan group
 constexpr int kMaxGroups = 4096;              // 2^31 parameters need 2048
-constexpr int kFusedTopGroups = 64;           // up to 64 groups: group scan fused into the scan launch
+constexpr int kEarlyGroups = 64;              // up to 64 groups: the scatter's EARLY form
 
 __host__ __device__ inline int64_t n_chunks(int64_t P) { return (P + 3) / 4; }
 int64_t n_tiles(int64_t P) { return (n_chunks(P) + kChunksPerTile - 1) / kChunksPerTile; }
@@ -96,8 +95,6 @@ __device__ __forceinline__ SelectArgs push_args(const SelectArgs& a0, const Sele
     a.tile_count = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(a0.tile_count) + off);
     a.tile_offset = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(a0.tile_offset) + off);
     a.group_total = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(a0.group_total) + off);
-    a.group_offset = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(a0.group_offset) + off);
-    a.groups_done = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(a0.groups_done) + off);
     return a;
 }
 
@@ -286,8 +283,6 @@ __global__ __launch_bounds__(kSelBlock) void select_mark_shared(const SelectArgs
 {
     const int b0 = blockIdx.y * G;
     const int nb = B - b0 < G ? B - b0 : G;
-    if (blockIdx.x == 0 && static_cast<int>(threadIdx.x) < nb)   // for the scan launch
-        *push_args(a0, bt, b0 + threadIdx.x).groups_done = 0u;
     const int64_t tile = wave_tile();
     if (tile >= a0.n_tiles) return;
     mark_pushes<true>(a0, bt, b0, nb, tile, threadIdx.x & (kWave - 1), true, nullptr, 0);
@@ -296,7 +291,6 @@ __global__ __launch_bounds__(kSelBlock) void select_mark_shared(const SelectArgs
 __global__ __launch_bounds__(kSelBlock) void select_mark(const SelectArgs a0, const SelectBatch bt, bool aligned)
 {
     const SelectArgs a = push_args(a0, bt, blockIdx.y);
-    if (blockIdx.x == 0 && threadIdx.x == 0) *a.groups_done = 0u;   // for the scan launch
     const int64_t tile = wave_tile();
     if (tile >= a.n_tiles) return;
     const int lane = threadIdx.x & (kWave - 1);
@@ -342,34 +336,8 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t* t
     return inc - x + (wave > 0 ? wave_total[wave - 1] : 0u);
 }
 
-// Offsets of the groups (at most kMaxGroups) from their totals, and the
-// number transmitted; run by one block.
-__device__ __forceinline__ void scan_groups(const SelectArgs& a, int64_t ng, bool atomic_loads)
-{
-    uint32_t carry = 0;
-    for (int64_t base = 0; base < ng; base += kScanBlock) {
-        const int64_t g = base + threadIdx.x;
-        uint32_t c = 0;
-        if (g < ng)
-            c = atomic_loads ? __hip_atomic_load(a.group_total + g, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT)
-                             : a.group_total[g];
-        uint32_t total;
-        const uint32_t off = block_exclusive_scan(c, &total);
-        if (g < ng) a.group_offset[g] = carry + off;
-        carry += total;
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        *a.d_count = static_cast<int64_t>(carry);
-        if (a.seg_start) a.seg_start[a.n_segs] = carry;
-    }
-}
-
 // Group g of 1024 tiles: offsets of its tiles within the group and the group
-// total.  FUSED_TOP: the last group block to arrive (arrival counter, zeroed
-// by the mark launch before this one) then scans the group totals itself.
-// Each arrival is a device-scope release, which costs more than a launch once
-// there are many groups; then select_top does that scan as its own launch.
+// total; select_scatter sums the totals of the groups before its own.
 // FROM_BALLOTS: the tile counts were not written (the mark step ran inside
 // another pass); count the tiles' ballot bits instead.  The wave's 64 tiles
 // are 8 KB of ballot words, read in 8 rounds of one 16-byte piece per lane
@@ -400,7 +368,7 @@ __device__ __forceinline__ uint32_t wave_tile_bits(const SelectArgs& a, int64_t 
     return s_cnt[w][lane];
 }
 
-template <bool FUSED_TOP, bool FROM_BALLOTS>
+template <bool FROM_BALLOTS>
 __global__ __launch_bounds__(kScanBlock) void select_scan(const SelectArgs a0, const SelectBatch bt)
 {
     const SelectArgs a = push_args(a0, bt, blockIdx.y);
@@ -416,25 +384,7 @@ __global__ __launch_bounds__(kScanBlock) void select_scan(const SelectArgs a0, c
     uint32_t total;
     const uint32_t off = block_exclusive_scan(c, &total);
     if (t < a.n_tiles) a.tile_offset[t] = off;
-    if (!FUSED_TOP) {
-        if (threadIdx.x == 0) a.group_total[blockIdx.x] = total;
-        return;
-    }
-    __shared__ bool last;
-    if (threadIdx.x == 0) {
-        __hip_atomic_store(a.group_total + blockIdx.x, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // release: the total is visible before the arrival is counted
-        const uint32_t before = __hip_atomic_fetch_add(a.groups_done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        last = before == gridDim.x - 1;
-    }
-    __syncthreads();
-    if (last) scan_groups(a, gridDim.x, true);
-}
-
-__global__ __launch_bounds__(kScanBlock) void select_top(const SelectArgs a0, const SelectBatch bt)
-{
-    const SelectArgs a = push_args(a0, bt, blockIdx.y);
-    scan_groups(a, (a.n_tiles + kScanBlock - 1) / kScanBlock, false);
+    if (threadIdx.x == 0) a.group_total[blockIdx.x] = total;
 }
 
 // Scatter one tile; FULL as for mark_tile.  The tile's entries are staged
@@ -545,9 +495,56 @@ __device__ __forceinline__ void scatter_loaded(const SelectArgs& a, int64_t tile
     }
 }
 
+// The list position of a tile's first entry: the totals of the groups before
+// its own, 256 of them (one 16-byte load per lane) at a time, and the tile's
+// offset within its group.  The first kGroupLoads loads are issued before the
+// tile's gradient loads, so that waiting for them leaves the gradients in
+// flight; 4 cover 1024 groups, 1.07e9 parameters.  Against a launch that
+// scanned the totals (up to 64 groups: the last scan block to arrive did), the
+// whole selection at 10 %, same box: 52M 91.9 -> 88.4 us, 100M 172.8 -> 165.5,
+// 300M 519 -> 508; at 1e9 equal.
+constexpr int kGroupLoads = 4;        // EARLY: 1
+
+__device__ __forceinline__ uint4 load_totals(const SelectArgs& a, int k, int n, int lane)
+{
+    // groups at or past n do not count; a lane that holds none of the others reads nothing
+    const int g = 4 * (lane + kWave * k);
+    return g < n ? reinterpret_cast<const uint4*>(a.group_total)[lane + kWave * k] : make_uint4(0u, 0u, 0u, 0u);
+}
+
+__device__ __forceinline__ uint32_t sum_totals(const uint4& x, int k, int n, int lane)
+{
+    const int g = 4 * (lane + kWave * k);
+    return (g < n ? x.x : 0u) + (g + 1 < n ? x.y : 0u) + (g + 2 < n ? x.z : 0u) + (g + 3 < n ? x.w : 0u);
+}
+
+template <int GL>
+__device__ __forceinline__ int64_t group_position(const SelectArgs& a, const uint4 (&tv)[GL], int n, int lane)
+{
+    uint32_t s = 0;
+#pragma unroll
+    for (int k = 0; k < GL; ++k)
+        if (4 * kWave * k < n) s += sum_totals(tv[k], k, n, lane);   // wave-uniform
+    for (int k = GL; 4 * kWave * k < n; ++k) s += sum_totals(load_totals(a, k, n, lane), k, n, lane);
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(wave_inclusive_scan(s)), kWave - 1));
+}
+
+// The call's count (and the list index's last entry) from the last tile.
+template <typename Words>
+__device__ __forceinline__ void finish_list(const SelectArgs& a, int64_t tile, int lane, const Words& bw, int64_t base)
+{
+    if (tile == a.n_tiles - 1 && lane == 0) {
+        uint32_t mine = 0;
+#pragma unroll
+        for (int k = 0; k < kTileWords; ++k) mine += __popcll(bw[k]);
+        *a.d_count = base + mine;
+        if (a.seg_start) a.seg_start[a.n_segs] = static_cast<uint32_t>(base + mine);
+    }
+}
+
 // EARLY: every ballot word and the list position are loaded and waited for
 // while the gradient loads are in flight.  In calls of at most
-// kFusedTopGroups groups (up to 67M parameters: the scan after a pass that
+// kEarlyGroups groups (up to 67M parameters: the scan after a pass that
 // took the decisions, and standalone calls past the two-launch form) every
 // wave's latency is exposed, and this took the 25M selection, then in three
 // launches, from 44.0-46.6 to 41.5-45.1 us (same box, lists identical).  Otherwise the compiler issues each part
@@ -558,22 +555,32 @@ template <bool FULL, bool EARLY>
 __device__ __forceinline__ void scatter_tile(const SelectArgs& a, int64_t tile, int lane, int32_t* s_idx,
                                              float* s_val)
 {
+    const int n = static_cast<int>(tile / kScanBlock);   // groups before this tile's
+    constexpr int GL = EARLY ? 1 : kGroupLoads;
+    uint4 tv[GL];
+#pragma unroll
+    for (int k = 0; k < GL; ++k)
+        tv[k] = 4 * kWave * k < n ? load_totals(a, k, n, lane) : make_uint4(0u, 0u, 0u, 0u);
+    __builtin_amdgcn_sched_barrier(0);
     f4 g[kTileSegs];
     load_tile_grad<FULL>(a, tile, lane, g);
-    const uint32_t group_off = a.group_offset[tile / kScanBlock];
     const uint32_t tile_off = a.tile_offset[tile];
-    const int64_t base = static_cast<int64_t>(group_off) + tile_off;
-    if (EARLY) {
+    if (EARLY && FULL) {
         uint64_t bw[kTileWords];
         load_tile_ballots(a, tile, bw);
         // uses that keep the compiler from sinking these loads to the first
         // use of each
 #pragma unroll
         for (int k = 0; k < kTileWords; ++k) asm volatile("" ::"s"(bw[k]));
-        asm volatile("" ::"s"(base));
+        asm volatile("" ::"s"(tile_off));
+        const int64_t base = group_position(a, tv, n, lane) + tile_off;
         scatter_loaded(a, tile, lane, g, bw, base, s_idx, s_val);
+        finish_list(a, tile, lane, bw, base);
     } else {
-        scatter_loaded(a, tile, lane, g, a.ballots + tile * kTileWords, base, s_idx, s_val);
+        const int64_t base = group_position(a, tv, n, lane) + tile_off;
+        const uint64_t* bw = a.ballots + tile * kTileWords;
+        scatter_loaded(a, tile, lane, g, bw, base, s_idx, s_val);
+        finish_list(a, tile, lane, bw, base);
     }
 }
 
@@ -728,20 +735,6 @@ __device__ __forceinline__ int64_t direct_position(const uint4 (&tv)[KT], int bl
     return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(inc), kWave - 1)) + tile_off;
 }
 
-// The call's count (and the list index's last entry) from the last tile.
-template <typename Words>
-__device__ __forceinline__ void direct_finish(const SelectArgs& a, int64_t tile, int lane, const Words& bw,
-                                              int64_t base)
-{
-    if (tile == a.n_tiles - 1 && lane == 0) {
-        uint32_t mine = 0;
-#pragma unroll
-        for (int k = 0; k < kTileWords; ++k) mine += __popcll(bw[k]);
-        *a.d_count = base + mine;
-        if (a.seg_start) a.seg_start[a.n_segs] = static_cast<uint32_t>(base + mine);
-    }
-}
-
 // FULL as for mark_tile.  The partial tile (or every tile of misaligned
 // arrays) finds its position before it loads its gradients, and reads its
 // ballot words from the workspace where it uses them, which needs fewer
@@ -772,13 +765,13 @@ __device__ __forceinline__ void scatter_direct_tile(const SelectArgs& a, int64_t
         asm volatile("" ::"s"(tile_off));
         const int64_t base = direct_position<KT>(tv, nb, tile_off, lane);
         scatter_loaded(a, tile, lane, g, bw, base, s_idx, s_val);
-        direct_finish(a, tile, lane, bw, base);
+        finish_list(a, tile, lane, bw, base);
     } else {
         const int64_t base = direct_position<KT>(tv, nb, a.tile_offset[tile], lane);
         load_tile_grad<false>(a, tile, lane, g);
         const uint64_t* bw = a.ballots + tile * kTileWords;
         scatter_loaded(a, tile, lane, g, bw, base, s_idx, s_val);
-        direct_finish(a, tile, lane, bw, base);
+        finish_list(a, tile, lane, bw, base);
     }
 }
 
@@ -988,10 +981,6 @@ void select_workspace_layout(void* ws, int64_t P, SelectArgs& a)
     a.tile_offset = reinterpret_cast<uint32_t*>(p);
     p += align256(size_t(nt) * sizeof(uint32_t));
     a.group_total = reinterpret_cast<uint32_t*>(p);
-    p += align256(size_t(kMaxGroups) * sizeof(uint32_t));
-    a.group_offset = reinterpret_cast<uint32_t*>(p);
-    p += align256(size_t(kMaxGroups) * sizeof(uint32_t));
-    a.groups_done = reinterpret_cast<uint32_t*>(p);
     a.n_tiles = nt;
 }
 
@@ -1011,17 +1000,10 @@ hipError_t launch_select(const SelectArgs& a, const SelectBatch& bt, int B, bool
         select_mark<<<grid, kSelBlock, 0, s>>>(a, bt, aligned);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (groups <= static_cast<unsigned>(kFusedTopGroups)) {
-        select_scan<true, false><<<dim3(groups, B), kScanBlock, 0, s>>>(a, bt);
-    } else {
-        select_scan<false, false><<<dim3(groups, B), kScanBlock, 0, s>>>(a, bt);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        select_top<<<dim3(1, B), kScanBlock, 0, s>>>(a, bt);
-    }
+    select_scan<false><<<dim3(groups, B), kScanBlock, 0, s>>>(a, bt);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (groups <= static_cast<unsigned>(kFusedTopGroups))
+    if (groups <= static_cast<unsigned>(kEarlyGroups))
         select_scatter<true><<<grid, kSelBlock, 0, s>>>(a, bt, aligned);
     else
         select_scatter<false><<<grid, kSelBlock, 0, s>>>(a, bt, aligned);
@@ -1037,18 +1019,10 @@ hipError_t launch_select_after_mark(const SelectArgs& a, bool aligned, hipStream
     memset(&bt, 0, sizeof bt);
     if (a.n_tiles <= 8 * kDirectMaxBlocks) return launch_direct<8>(a, bt, 1, aligned, true, s);
     if (a.n_tiles <= kDirectMaxTiles) return launch_direct<16>(a, bt, 1, aligned, true, s);
-    hipError_t e;
-    if (groups <= static_cast<unsigned>(kFusedTopGroups)) {
-        select_scan<true, true><<<groups, kScanBlock, 0, s>>>(a, bt);
-    } else {
-        select_scan<false, true><<<groups, kScanBlock, 0, s>>>(a, bt);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        select_top<<<1, kScanBlock, 0, s>>>(a, bt);
-    }
-    e = hipGetLastError();
+    select_scan<true><<<groups, kScanBlock, 0, s>>>(a, bt);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (groups <= static_cast<unsigned>(kFusedTopGroups))
+    if (groups <= static_cast<unsigned>(kEarlyGroups))
         select_scatter<true><<<gx, kSelBlock, 0, s>>>(a, bt, aligned);
     else
         select_scatter<false><<<gx, kSelBlock, 0, s>>>(a, bt, aligned);

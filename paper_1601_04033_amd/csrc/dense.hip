@@ -304,7 +304,6 @@ __global__ __launch_bounds__(kBlock) void fasgd_dense_push_vec(const DenseArgs a
         }
     }
     if (MARK) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) *m.groups_done = 0u;   // for the scan launch
         const int n_own = own ? 4 : (i == nvec ? static_cast<int>(a.P - 4 * nvec) : 0);
         uint32_t nib = 0;
         if (n_own > 0) {
@@ -628,7 +627,6 @@ __global__ __launch_bounds__(kLaneBlock) void fasgd_dense_push_lane(const DenseA
         stnt(a.v + j, v);
     }
     if (MARK) {
-        if (blockIdx.x == 0 && t == 0) *m.groups_done = 0u;   // for the scan launch
         const int lane = t & (kWave - 1);
         const int w = __builtin_amdgcn_readfirstlane(t / kWave);
         uint32_t bit = 0;

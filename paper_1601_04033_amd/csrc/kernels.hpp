@@ -57,8 +57,6 @@ struct SelectArgs {
     uint32_t* tile_count;
     uint32_t* tile_offset;   // within its group of 1024 tiles
     uint32_t* group_total;
-    uint32_t* group_offset;
-    uint32_t* groups_done;  // arrival counter of the scan blocks
     int64_t P;
     int64_t capacity;
     int64_t n_tiles;
@@ -85,9 +83,10 @@ struct SelectBatch {
 };
 
 // Workspace of one selection: 16 ballot words (8 bytes each) per wave tile
-// of kSelTileParams parameters, a count and an offset per tile, the totals
-// and offsets of at most kSelMaxGroups groups of tiles, and an arrival
-// counter, each part 256-byte aligned.
+// of kSelTileParams parameters, a count and an offset per tile and the totals
+// of at most kSelMaxGroups groups of tiles, each part 256-byte aligned (the
+// rest, as much again and 256 bytes, is no longer used: callers' workspaces
+// keep their size).
 constexpr int64_t kSelTileParams = 1024;
 constexpr int kSelTileWords = 16;
 constexpr int kSelMaxGroups = 4096;
