@@ -556,6 +556,18 @@ fasgd_status fasgd_apply_with_push(fasgd_state* st, const int32_t* push_idx, con
     return ok();
 }
 
+namespace {
+// The next push's decisions ride on the pass, which saves a read of v, except
+// in IEEE math from 8 gradients on: there the pass is as busy with arithmetic
+// as with memory, each of its threads draws its chunk's Philox call (four
+// times over), and the selection's own mark launch is the cheaper place.
+// The step with the decisions in the pass against apart: 25M, K = 4 229
+// against 236 us, 8 301 against 298, 32 760 against 736; 100M, K = 4 903
+// against 937, 8 1189 against 1189, 32 3042 against 2958; 2M, K = 8 36.0
+// against 33.3, 32 74.1 against 67.7.
+constexpr int kDecideApartFrom = 8;
+}  // namespace
+
 fasgd_status fasgd_apply_with_push_and_select(fasgd_state* st, const int32_t* push_idx, const float* push_val,
                                               const int64_t* push_count, const uint32_t* push_seg_start,
                                               int64_t push_capacity, int32_t push_client, int64_t push_grad_ts,
@@ -583,12 +595,15 @@ fasgd_status fasgd_apply_with_push_and_select(fasgd_state* st, const int32_t* pu
     s = select_setup(&after, 1, &next_grad, c, eps_c, seed, &T_next, &next_client, out_idx, out_val, out_capacity,
                      out_count, out_seg_start, workspace, workspace_bytes, m, bt, sel_vec);
     if (s != FASGD_OK) return s;
-    // the pass takes the decisions; the selection's own launches scan them
-    // and scatter
+    // the pass takes the decisions and the selection's own launches scan them
+    // and scatter, or the selection follows whole
+    const bool apart = st->math_mode == FASGD_MATH_IEEE && K >= kDecideApartFrom;
     hipError_t e = pass_begin(stream);
-    if (e == hipSuccess) e = fasgd::launch_fasgd_dense_push(a, p, &m, variant_of(st), vec, stream);
+    if (e == hipSuccess) e = fasgd::launch_fasgd_dense_push(a, p, apart ? nullptr : &m, variant_of(st), vec, stream);
     if (e == hipSuccess) e = pass_end(stream);
-    if (e == hipSuccess) e = fasgd::launch_select_after_mark(m, aligned(next_grad, 16), stream);
+    if (e == hipSuccess)
+        e = apart ? fasgd::launch_select(m, bt, 1, sel_vec, stream)
+                  : fasgd::launch_select_after_mark(m, aligned(next_grad, 16), stream);
     if (e != hipSuccess) return hip_fail(e, "fasgd_apply_with_push_and_select");
     st->dense_T = st->T + K;
     st->T += K + 1;

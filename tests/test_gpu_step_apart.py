@@ -1,0 +1,47 @@
+"""GPU: the server's step in IEEE math around the number of gradients from
+which its decisions are taken apart from the pass, against the two calls, bit
+for bit, with the next push's list over the one being applied."""
+import numpy as np
+import pytest
+
+import paper_1601_04033_amd as fa
+from helpers import gpu, new_gpu_state
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("P,off", [(1025, 0), (4099, 1), (300_002, 0)])
+@pytest.mark.parametrize("K", [7, 8, 9])
+def test_step_equals_two_calls(P, off, K):
+    import torch
+    dev = gpu()
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(P + K)
+    theta0 = np.random.default_rng(P).standard_normal(P, dtype=np.float32)
+    # off = 1: gradients 4 bytes past a 16-byte boundary
+    grads = [(torch.randn(P + off, device=dev, generator=gen) * 1e-2)[off:] for _ in range(K + 2)]
+    clients, L = [k % 4 for k in range(K)], fa.bfasgd_list_index_length(P)
+    out = []
+    for together in (True, False):
+        st = new_gpu_state(theta0, dev, 4, 0.005, fa.MATH_IEEE, v0=3.0)
+        st.c.T, st.c.dense_T = 60, 59
+        idx, val = torch.zeros(P, device=dev, dtype=torch.int32), torch.zeros(P, device=dev)
+        cnt = torch.zeros(1, device=dev, dtype=torch.int64)
+        seg = torch.zeros(L, device=dev, dtype=torch.int32)
+        ws = torch.full((fa.bfasgd_workspace_bytes(P),), 0xA5, device=dev, dtype=torch.uint8)
+        fa.bfasgd_select_compact(st, grads[K], 20.0, 1e-8, 9, st.T, 1, idx, val, cnt, ws, seg_start=seg)
+        for _ in range(2):
+            T = st.T
+            ts = [T + 1 + k - k % 3 for k in range(K)]
+            if together:
+                fa.fasgd_apply_with_push_and_select(st, idx, val, cnt, seg, 1, T - 2, grads[:K], clients, ts,
+                                                    grads[K + 1], 2, 20.0, 1e-8, 9, idx, val, cnt, seg, ws)
+            else:
+                fa.fasgd_apply_with_push(st, idx, val, cnt, seg, 1, T - 2, grads[:K], clients, ts)
+                fa.bfasgd_select_compact(st, grads[K + 1], 20.0, 1e-8, 9, st.T, 2, idx, val, cnt, ws, seg_start=seg)
+        torch.cuda.synchronize()
+        m = int(cnt.item())
+        assert 0 < m < P and st.T == 60 + 2 * (K + 1)
+        out.append([st.tensors[n].view(torch.int32) for n in ("theta", "n", "b", "v")] + [idx[:m], val[:m].view(torch.int32), seg])
+    for x, y in zip(*out):
+        assert torch.equal(x, y)
