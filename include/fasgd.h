@@ -314,9 +314,10 @@ fasgd_status fasgd_apply_with_push(fasgd_state* st, const int32_t* push_idx, con
  * workspace_bytes) with T' = the timestamp after the pass (the one the next
  * pass applies that push at) and v as the pass leaves it.  Every output
  * (theta, n, b, v, T, dense_T, the list, its count and its index) is
- * bit-identical to those two calls; when the state and the K gradients are
- * 16-byte aligned the pass itself takes the next push's transmit decisions
- * from the v it holds in registers, so the selection does not read v again.
+ * bit-identical to those two calls; the pass itself takes the next push's
+ * transmit decisions from the v it holds in registers, so the selection does
+ * not read v again (except in IEEE math from 8 gradients on, where the
+ * selection on its own is faster).
  * The output list may be the buffers of the push being applied (the pass
  * reads them before the selection writes).
  *   push_*, grads, clients, grad_ts, K  as for fasgd_apply_with_push
