@@ -65,9 +65,17 @@ struct Args {
     Args(const Args&) = delete;
     Args& operator=(const Args&) = delete;
 
+    // The argument is not plain.  Of the exceptions that its conversion may
+    // have raised, those that say so are dropped, as the general way raises
+    // them again; any other (an interrupt, a signal handler's, no memory)
+    // stays set, and finish() lets it out.
     bool refuse()
     {
-        if (PyErr_Occurred()) PyErr_Clear();
+        if (PyErr_Occurred() &&
+            (PyErr_ExceptionMatches(PyExc_TypeError) || PyErr_ExceptionMatches(PyExc_ValueError) ||
+             PyErr_ExceptionMatches(PyExc_OverflowError) || PyErr_ExceptionMatches(PyExc_AttributeError) ||
+             PyErr_ExceptionMatches(PyExc_BufferError)))
+            PyErr_Clear();
         plain = false;
         return false;
     }
@@ -252,7 +260,16 @@ struct Args {
     hipStream_t stream(int i)
     {
         if (!plain) return nullptr;
-        PyObject* h = v[i] == Py_None ? PyObject_CallNoArgs(g_current_stream) : PyObject_GetAttrString(v[i], "cuda_stream");
+        PyObject* h;
+        if (v[i] == Py_None) {
+            h = PyObject_CallNoArgs(g_current_stream);
+            if (!h) {   // whatever it raises is the call's
+                plain = false;
+                return nullptr;
+            }
+        } else {
+            h = PyObject_GetAttrString(v[i], "cuda_stream");
+        }
         if (!h || !PyLong_Check(h)) {
             Py_XDECREF(h);
             refuse();
@@ -267,11 +284,15 @@ struct Args {
 
 int64_t index_length(int64_t P) { return P < 1 ? 0 : (P + 255) / 256 + 1; }
 
-// The library call itself, without the interpreter's lock; None unless the arguments were plain.
+// The library call itself, without the interpreter's lock; None unless the arguments were plain, or the exception
+// that a getter left set.
 template <typename Call>
 PyObject* finish(Args& a, Call call)
 {
-    if (!a.plain) Py_RETURN_NONE;
+    if (!a.plain) {
+        if (PyErr_Occurred()) return nullptr;
+        Py_RETURN_NONE;
+    }
     int rc;
     Py_BEGIN_ALLOW_THREADS
     rc = static_cast<int>(call());

@@ -251,3 +251,51 @@ def test_wrong_arity_and_binding_are_errors():
         native.bind([0] * len(SIGNATURES), fa._current_stream)
     with pytest.raises(ValueError):
         native.bind([1], fa._current_stream)
+
+
+class Raises:
+    """A number whose conversion raises."""
+
+    def __init__(self, e):
+        self.e = e
+
+    def __index__(self):
+        raise self.e
+
+    __int__ = __index__
+
+
+@pytest.mark.parametrize("e", [KeyboardInterrupt, MemoryError, RuntimeError, SystemExit])
+def test_exceptions_that_are_no_refusal_come_out(recorder, e):
+    """What a signal handler (or the interpreter) raises while a number is converted ends the call."""
+    import torch
+    t = things(torch.device("cpu"))
+    st, off = t["st"], t["off"]
+    native = fa._native()
+    with pytest.raises(e):
+        native.bfasgd_decide_segments(st.c, off, 1.0, 1e-8, 3, Raises(e()), 5, t["send"], t["ws"], None)
+    with pytest.raises(e):
+        native.fasgd_apply_pushes(st.c, t["bidx"], t["bval"], t["bcnt"], t["bseg"], [0, Raises(e()), 2], [0, 0, 0], None)
+    with pytest.raises(e):
+        native.fasgd_apply_pushes(st.c, t["bidx"], t["bval"], t["bcnt"], t["bseg"], [0, 1, 2], [0, 0, Raises(e())], None)
+    # those that say "not plain" are the general way's to raise
+    for mild in (TypeError(), ValueError(), OverflowError()):
+        assert native.bfasgd_decide_segments(st.c, off, 1.0, 1e-8, 3, Raises(mild), 5, t["send"], t["ws"], None) is None
+    assert not recorder.calls
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("e", [KeyboardInterrupt, TypeError])
+def test_the_stream_lookup_s_exception_comes_out(recorder, e):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    t = things(torch.device("cuda:0"))
+    native = fa._native()
+
+    def lookup():
+        raise e()
+    native.bind([ctypes.cast(getattr(recorder, n), ptr).value for n in native.ENTRY_POINTS], lookup)
+    with pytest.raises(e):                       # the recorder's fixture binds the library again
+        fa.bfasgd_apply_sparse(t["st"], t["idx"], t["val"], t["cnt"], 3, 50)
+    assert not recorder.calls
