@@ -198,8 +198,9 @@ struct Args {
         return static_cast<float>(d);
     }
 
-    // the items of a sequence of n (n < 0: any number, 1 .. most); lists and tuples are taken as they are
-    PyObject** items(int i, int64_t n, int64_t most, int64_t* count)
+    // a sequence of n (n < 0: any number, 1 .. most); lists and tuples are taken as they are, so a list's items are
+    // read through integer_at() wherever Python code may have run since
+    PyObject* sequence(int i, int64_t n, int64_t most, int64_t* count)
     {
         if (!plain) return nullptr;
         if (!PyList_CheckExact(v[i]) && !PyTuple_CheckExact(v[i]) && !PySequence_Check(v[i])) {
@@ -218,25 +219,39 @@ struct Args {
             return nullptr;
         }
         if (count) *count = k;
-        return PySequence_Fast_ITEMS(f);
+        return f;
+    }
+    // the integer at place k of a sequence: its conversion may run Python code, which may change the sequence
+    int64_t integer_at(PyObject* f, int64_t k)
+    {
+        if (!plain) return 0;
+        if (k >= PySequence_Fast_GET_SIZE(f)) {
+            refuse();
+            return 0;
+        }
+        PyObject* o = PySequence_Fast_GET_ITEM(f, k);
+        Py_INCREF(o);
+        const int64_t r = integer_of(o);
+        Py_DECREF(o);
+        return r;
     }
     int64_t gradients(int i, int64_t P, const float** out, int64_t most)
     {
         int64_t K = 0;
-        PyObject** it = items(i, -1, most, &K);
-        for (int64_t k = 0; plain && k < K; ++k)
-            out[k] = static_cast<const float*>(tensor_of(it[k], c10::ScalarType::Float, P));
+        PyObject* f = sequence(i, -1, most, &K);
+        for (int64_t k = 0; plain && k < K; ++k)   // no Python code runs in between
+            out[k] = static_cast<const float*>(tensor_of(PySequence_Fast_GET_ITEM(f, k), c10::ScalarType::Float, P));
         return K;
     }
     void clients(int i, int64_t K, int32_t* out)
     {
-        PyObject** it = items(i, K, K, nullptr);
-        for (int64_t k = 0; plain && k < K; ++k) out[k] = narrow(integer_of(it[k]));
+        PyObject* f = sequence(i, K, K, nullptr);
+        for (int64_t k = 0; plain && k < K; ++k) out[k] = narrow(integer_at(f, k));
     }
     void timestamps(int i, int64_t K, int64_t* out)
     {
-        PyObject** it = items(i, K, K, nullptr);
-        for (int64_t k = 0; plain && k < K; ++k) out[k] = integer_of(it[k]);
+        PyObject* f = sequence(i, K, K, nullptr);
+        for (int64_t k = 0; plain && k < K; ++k) out[k] = integer_at(f, k);
     }
     // host offsets of S + 1 segments: a C-contiguous one-dimensional int64 array
     const int64_t* segments(int i, int32_t* S)
@@ -471,8 +486,8 @@ PyObject* apply_pushes(PyObject*, PyObject* const* args, Py_ssize_t n)
     const int64_t P = st ? st->P : 0;
     int32_t cl[FASGD_MAX_BATCH];
     int64_t ts[FASGD_MAX_BATCH], B = 0;
-    PyObject** it = a.items(5, -1, FASGD_MAX_BATCH, &B);
-    for (int64_t b = 0; a.plain && b < B; ++b) cl[b] = a.narrow(a.integer_of(it[b]));
+    PyObject* f = a.sequence(5, -1, FASGD_MAX_BATCH, &B);
+    for (int64_t b = 0; a.plain && b < B; ++b) cl[b] = a.narrow(a.integer_at(f, b));
     a.timestamps(6, B, ts);
     const int64_t cap = a.columns(1, B);
     a.columns(2, B);

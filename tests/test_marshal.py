@@ -299,3 +299,24 @@ def test_the_stream_lookup_s_exception_comes_out(recorder, e):
     with pytest.raises(e):                       # the recorder's fixture binds the library again
         fa.bfasgd_apply_sparse(t["st"], t["idx"], t["val"], t["cnt"], 3, 50)
     assert not recorder.calls
+
+
+def test_a_list_that_shrinks_while_it_is_read(recorder):
+    """A number whose conversion shortens its own list: the list's new length is seen, and the call is refused."""
+    import torch
+    t = things(torch.device("cpu"))
+    seen = []
+
+    class Shrinks:
+        def __index__(self):
+            del clients[1:]
+            return 1
+
+    class Seen:
+        def __index__(self):
+            seen.append(1)
+            return 2
+    clients = [Shrinks(), 1, 2]
+    assert fa._native().fasgd_apply_pushes(t["st"].c, t["bidx"], t["bval"], t["bcnt"], t["bseg"], clients, [Seen(), 1, 1],
+                                           None) is None
+    assert len(clients) == 1 and not seen and not recorder.calls
