@@ -627,6 +627,8 @@ def bfasgd_apply_segments(state: State, grad, seg, d_transmit, client: int, grad
     arr, ptr, S = _seg_array(seg)
     if grad.numel() != state.P:
         raise ValueError("grad length differs from P")
+    if d_transmit.numel() < S:
+        raise ValueError("d_transmit needs one entry per segment")
     rc = load_library().bfasgd_apply_segments(
         ctypes.byref(state.c), _dev_ptr(grad, torch.float32, "grad"), ptr, S,
         _dev_ptr(d_transmit, torch.uint8, "d_transmit"), int(client), int(grad_ts), _stream(stream))

@@ -566,7 +566,7 @@ PyObject* apply_segments(PyObject*, PyObject* const* args, Py_ssize_t n)
     int32_t S = 0;
     const float* g = a.floats(1, st ? st->P : 0);
     const int64_t* seg = a.segments(2, &S);
-    const uint8_t* send = static_cast<const uint8_t*>(a.tensor(3, c10::ScalarType::Byte, -1));
+    const uint8_t* send = static_cast<const uint8_t*>(a.tensor(3, c10::ScalarType::Byte, -1, S));   // one byte per segment
     const int32_t client = a.int32(4);
     const int64_t ts = a.int64(5);
     hipStream_t s = a.stream(6);

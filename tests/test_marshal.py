@@ -320,3 +320,27 @@ def test_a_list_that_shrinks_while_it_is_read(recorder):
     assert fa._native().fasgd_apply_pushes(t["st"].c, t["bidx"], t["bval"], t["bcnt"], t["bseg"], clients, [Seen(), 1, 1],
                                            None) is None
     assert len(clients) == 1 and not seen and not recorder.calls
+
+
+def test_a_short_transmit_array_is_rejected(recorder):
+    """The segment apply reads one byte per segment: an array made for fewer segments does not reach the library."""
+    import torch
+    t = things(torch.device("cpu"))
+    with pytest.raises(ValueError, match="one entry per segment"):
+        fa.bfasgd_apply_segments(t["st"], t["g"][0], t["off"], t["send"][:1], 5, 6)
+    assert not recorder.calls
+
+
+@pytest.mark.gpu
+def test_transmit_arrays_on_the_device(recorder):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    t = things(torch.device("cuda:0"))
+    for off in (t["off"], t["off"].tolist()):    # the native and the general way
+        with pytest.raises(ValueError, match="one entry per segment"):
+            fa.bfasgd_apply_segments(t["st"], t["g"][0], off, t["send"][:1], 5, 6)
+        assert not recorder.calls
+        fa.bfasgd_apply_segments(t["st"], t["g"][0], off, torch.zeros(3, device="cuda:0", dtype=torch.uint8), 5, 6)
+        assert len(recorder.calls) == 1          # a longer array is taken
+        recorder.calls.clear()
