@@ -50,15 +50,26 @@ def build(verbose: bool = False, extra_flags=()) -> str:
     return LIB
 
 
-def build_marshal(verbose: bool = False) -> str:
-    """The native argument marshalling of the binding (csrc/marshal.cpp)."""
-    import torch
-    from torch.utils import cpp_extension
+def build_marshal(verbose: bool = False):
+    """The native argument marshalling of the binding (csrc/marshal.cpp).  The library does not need it: without a
+    host compiler, Python's headers or torch it is left out, and the binding marshals in Python."""
+    cxx = os.environ.get("CXX", "g++")
+    try:
+        import torch
+        from torch.utils import cpp_extension
+    except ImportError:
+        torch = None
+    if torch is None or not shutil.which(cxx) or not os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h")):
+        print(f"{os.path.basename(MARSHAL)} left out: it needs {cxx}, Python.h and torch", file=sys.stderr, flush=True)
+        if os.path.exists(MARSHAL):
+            os.remove(MARSHAL)      # an older build's
+        return None
     inc = [f"-I{d}" for d in (os.path.join(ROOT, "include"), *cpp_extension.include_paths(),
                               sysconfig.get_paths()["include"], "/opt/rocm/include")]
     tmp = MARSHAL + ".tmp"
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *inc,
+    cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DFASGD_TORCH_VERSION="{torch.__version__}"', *inc,
            os.path.join(CSRC, "marshal.cpp"), "-o", tmp, *[f"-L{d}" for d in cpp_extension.library_paths()],
            "-ltorch_python", "-ltorch_cpu", "-lc10"]
     if verbose:

@@ -627,5 +627,7 @@ PyMODINIT_FUNC PyInit__marshal()
     if (!names) return nullptr;
     for (int i = 0; i < kCount; ++i) PyTuple_SET_ITEM(names, i, PyUnicode_FromString(kNames[i]));
     if (PyModule_AddObject(m, "ENTRY_POINTS", names) != 0) return nullptr;
+    // at::Tensor's layout is that torch's alone
+    if (PyModule_AddStringConstant(m, "TORCH_VERSION", FASGD_TORCH_VERSION) != 0) return nullptr;
     return m;
 }

@@ -344,3 +344,45 @@ def test_transmit_arrays_on_the_device(recorder):
         fa.bfasgd_apply_segments(t["st"], t["g"][0], off, torch.zeros(3, device="cuda:0", dtype=torch.uint8), 5, 6)
         assert len(recorder.calls) == 1          # a longer array is taken
         recorder.calls.clear()
+
+
+@pytest.fixture
+def unbound(recorder, monkeypatch):
+    """The binding before its first call, on a recorder, with host tensors taken for device ones."""
+    monkeypatch.setattr(fa, "_calls", None)
+    monkeypatch.setattr(fa, "_dev_ptr", lambda t, *a: None if t is None else t.data_ptr())
+    monkeypatch.setattr(fa, "_stream", lambda stream: 0)
+    yield recorder
+
+
+def _every_call_is_served(recorder):
+    import torch
+    t = things(torch.device("cpu"))
+    with pytest.warns(RuntimeWarning, match="marshalled in Python") as seen:
+        for name, args, kw in forms(t):
+            getattr(fa, name)(*args, **kw)
+            assert recorder.calls.pop()[0] == name and not recorder.calls
+    assert len(seen) == 1
+
+
+def test_without_the_module_calls_are_marshalled_in_python(unbound, monkeypatch):
+    import sys
+    monkeypatch.delattr(fa, "_marshal", raising=False)
+    monkeypatch.setitem(sys.modules, fa.__name__ + "._marshal", None)     # its import fails
+    _every_call_is_served(unbound)
+
+
+def test_a_module_of_another_torch_is_not_used(unbound, monkeypatch):
+    import torch
+    monkeypatch.setattr(torch, "__version__", "0.1")
+    _every_call_is_served(unbound)
+
+
+def test_the_library_is_built_without_a_host_compiler(tmp_path, monkeypatch, capsys):
+    import paper_1601_04033_amd._build as lib_build
+    old = tmp_path / "_marshal.so"
+    old.write_bytes(b"")
+    monkeypatch.setattr(lib_build, "MARSHAL", str(old))
+    monkeypatch.setenv("CXX", "no-such-compiler")
+    assert lib_build.build_marshal() is None
+    assert "left out" in capsys.readouterr().err and not old.exists()
