@@ -177,22 +177,24 @@ struct Args {
         return static_cast<int32_t>(r);
     }
     int32_t int32(int i) { return narrow(integer_of(v[i])); }
+    // any integer, by its low 64 bits
     uint64_t seed(int i)
     {
         if (!plain) return 0;
-        if (!PyLong_CheckExact(v[i])) {
+        PyObject* x = PyNumber_Index(v[i]);
+        if (!x) {
             refuse();
             return 0;
         }
-        return PyLong_AsUnsignedLongLongMask(v[i]);
+        const uint64_t r = PyLong_AsUnsignedLongLongMask(x);
+        Py_DECREF(x);
+        if (PyErr_Occurred()) refuse();
+        return r;
     }
+    // what ctypes takes for a float: any number (numpy's too)
     float real(int i)
     {
         if (!plain) return 0.0f;
-        if (!PyFloat_CheckExact(v[i]) && !PyLong_CheckExact(v[i])) {
-            refuse();
-            return 0.0f;
-        }
         const double d = PyFloat_AsDouble(v[i]);
         if (d == -1.0 && PyErr_Occurred()) refuse();
         return static_cast<float>(d);
@@ -271,7 +273,7 @@ struct Args {
         *S = static_cast<int32_t>(seg_view.len / 8 - 1);
         return static_cast<const int64_t*>(seg_view.buf);
     }
-    // the stream's handle; None: the current stream (looked up last, after every tensor was found to be a device one)
+    // the stream's handle, or it itself; None: the current stream (looked up last, after every tensor was found to be a device one)
     hipStream_t stream(int i)
     {
         if (!plain) return nullptr;
@@ -282,6 +284,9 @@ struct Args {
                 plain = false;
                 return nullptr;
             }
+        } else if (PyLong_CheckExact(v[i])) {   // a raw handle
+            h = v[i];
+            Py_INCREF(h);
         } else {
             h = PyObject_GetAttrString(v[i], "cuda_stream");
         }

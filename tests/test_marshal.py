@@ -386,3 +386,33 @@ def test_the_library_is_built_without_a_host_compiler(tmp_path, monkeypatch, cap
     monkeypatch.setenv("CXX", "no-such-compiler")
     assert lib_build.build_marshal() is None
     assert "left out" in capsys.readouterr().err and not old.exists()
+
+
+@pytest.mark.parametrize("c,eps_c,seed", [(np.float64(1.0), np.float32(1e-8), np.int64(3)), (np.int32(1), 0, np.uint64(2 ** 63)),
+                                          (True, 1e-8, False)])
+def test_numpy_numbers_are_plain(recorder, c, eps_c, seed):
+    """Numbers that ctypes and int() convert are not left to the general way: the timestamp after them is reached."""
+    import torch
+    t = things(torch.device("cpu"))
+    with pytest.raises(KeyboardInterrupt):
+        fa._native().bfasgd_decide_segments(t["st"].c, t["off"], c, eps_c, seed, Raises(KeyboardInterrupt()), 5, t["send"],
+                                            t["ws"], None)
+
+
+@pytest.mark.gpu
+def test_raw_streams_and_numpy_numbers_are_marshalled_natively(recorder, monkeypatch):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    t = things(torch.device("cuda:0"))
+    st, g, idx, val, cnt, ws = (t[k] for k in ("st", "g", "idx", "val", "cnt", "ws"))
+    side = torch.cuda.Stream()
+    for s in (0, int(side.cuda_stream), side, None):
+        for args in ((st, g[0], np.float64(2.5), np.float32(1e-8), np.uint64(2 ** 64 - 1), 7, 3, idx, val, cnt, ws),
+                     (st, g[0], 0.1, 0, np.int64(-5), np.int64(7), np.int32(3), idx, val, cnt, ws)):
+            assert fa._native().bfasgd_select_compact(st.c, *args[1:], None, s) == 0
+            with monkeypatch.context() as m:
+                general(m)
+                fa.bfasgd_select_compact(*args, stream=s)
+            assert len(recorder.calls) == 2 and recorder.calls[0] == recorder.calls[1], (s, recorder.calls)
+            recorder.calls.clear()
