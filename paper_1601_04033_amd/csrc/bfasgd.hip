@@ -874,10 +874,8 @@ constexpr int64_t kListMaxBlocks = 65536;     // grid cap of the list kernels (g
 //   300M, 2 %        1632     1566     1549
 // (non-temporal loads of the state cost 30 %: a line's second reader misses).
 template <int MODE, int E, bool STREAM>
-__global__ __launch_bounds__(kListBlock) void sparse_apply(const SparseArgs a)
+__device__ __forceinline__ void sparse_runs(const SparseArgs& a, int64_t m)
 {
-    int64_t m = *a.d_count;
-    if (m > a.capacity) m = a.capacity;
     const Hyper h = a.h;
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t wave_id = (static_cast<int64_t>(blockIdx.x) * kListBlock + threadIdx.x) / kWave;
@@ -915,6 +913,33 @@ __global__ __launch_bounds__(kListBlock) void sparse_apply(const SparseArgs a)
             }
         }
     }
+}
+
+// A list too short to give each of the 256 CUs two runs of 64 E entries goes
+// in runs of 128: such an apply is bound by the latency of its gathers, and
+// long runs leave CUs idle.  A whole push, plain E = 2 at every length (an
+// earlier form), E = 6 at every length, and the line at 1, 2 and 4 runs per
+// CU, same box:
+//   P, transmitted          E = 2    E = 6     1       2       4
+//   17M, 0.3 % (51k)         46.1     56.4    45.7    44.6    45.8 us
+//   17M, 0.6 % (102k)        55.9     61.8    59.3    50.2    52.1
+//   25M, 0.4 % (100k)        69.5     73.1    71.7    62.9    62.5
+//   25M, 0.6 % (150k)        82.6     77.4    78.0    74.5    74.4
+//   100M, 0.1 % (100k)        173      177     174     164     165
+//   100M, 0.3 % (300k)        236      204     200     208     206
+//   400M, 0.1 % (400k)        650      633     628     628     632
+constexpr int kShortE = 2;
+constexpr int64_t short_list(int E) { return int64_t(2 * 256) * kWave * E; }
+
+template <int MODE, int E, bool STREAM>
+__global__ __launch_bounds__(kListBlock) void sparse_apply(const SparseArgs a)
+{
+    int64_t m = *a.d_count;
+    if (m > a.capacity) m = a.capacity;
+    if (E > kShortE && m < short_list(E))
+        sparse_runs<MODE, kShortE, STREAM>(a, m);
+    else
+        sparse_runs<MODE, E, STREAM>(a, m);
 }
 
 // The list's values into a dense array, one partial 32-byte sector per entry;
@@ -1035,6 +1060,11 @@ template <int MODE, int E, bool STREAM>
 void launch_sparse_shape(const SparseArgs& a, hipStream_t s)
 {
     int64_t g = (a.capacity + int64_t(kListBlock) * E - 1) / (int64_t(kListBlock) * E);
+    if (E > kShortE) {   // the shorter runs of a short list
+        const int64_t m = a.capacity < short_list(E) ? a.capacity : short_list(E);
+        const int64_t g_short = (m + int64_t(kListBlock) * kShortE - 1) / (int64_t(kListBlock) * kShortE);
+        if (g < g_short) g = g_short;
+    }
     if (g > kListMaxBlocks) g = kListMaxBlocks;
     if (g < 1) g = 1;
     sparse_apply<MODE, E, STREAM><<<static_cast<unsigned>(g), kListBlock, 0, s>>>(a);

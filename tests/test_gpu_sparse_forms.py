@@ -55,3 +55,34 @@ def test_sparse_apply_forms(P, mode):
     st = server()
     fa.bfasgd_apply_sparse(st, idx, grad[:500].contiguous(), torch.full((1,), P, device=dev, dtype=torch.int64), 1, 5)
     assert torch.equal(st.theta[:500], dense.theta[:500]) and torch.equal(st.theta[500:], theta0[500:])
+
+
+@pytest.mark.parametrize("mode", [fa.MATH_FAST, fa.MATH_IEEE])
+@pytest.mark.parametrize("m", [196_607, 196_608, 196_609, 300_001])
+@pytest.mark.parametrize("room", ["exact", "whole"])
+def test_sparse_apply_around_a_short_list(m, mode, room):
+    """Beyond 16M parameters, lists on both sides of 512 runs of 384 entries, in buffers of their own length and of P."""
+    import torch
+    dev = gpu()
+    P = 16_000_001
+    gen = torch.Generator(device=dev).manual_seed(m)
+    theta0 = torch.randn(P, device=dev, generator=gen)
+    grad = torch.randn(P, device=dev, generator=gen)
+
+    def server():
+        st = new_gpu_state(theta0, dev, 4, 0.005, mode)
+        st.v.fill_(3.0)
+        st.c.T, st.c.dense_T = 20, 19
+        return st
+
+    dense, st, fresh = server(), server(), server()
+    fa.fasgd_apply_updates(dense, [grad], [1], [5])
+    listed = torch.randperm(P, device=dev, generator=gen)[:m].sort().values
+    idx = torch.zeros(m if room == "exact" else P, device=dev, dtype=torch.int32)
+    val = torch.zeros(idx.numel(), device=dev)
+    idx[:m], val[:m] = listed.int(), grad[listed]
+    fa.bfasgd_apply_sparse(st, idx, val, torch.full((1,), m, device=dev, dtype=torch.int64), 1, 5)
+    for name in ("theta", "n", "b", "v", "last_T"):
+        want = fresh.tensors[name].clone()
+        want[listed] = 20 if name == "last_T" else dense.tensors[name][listed]
+        assert torch.equal(st.tensors[name].view(torch.int32), want.view(torch.int32)), name
