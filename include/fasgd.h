@@ -316,8 +316,8 @@ fasgd_status fasgd_apply_with_push(fasgd_state* st, const int32_t* push_idx, con
  * (theta, n, b, v, T, dense_T, the list, its count and its index) is
  * bit-identical to those two calls; the pass itself takes the next push's
  * transmit decisions from the v it holds in registers, so the selection does
- * not read v again (except in IEEE math from 8 gradients on, where the
- * selection on its own is faster).
+ * not read v again (except in IEEE math from 8 gradients on with v and
+ * next_grad 16-byte aligned, where the selection on its own is faster).
  * The output list may be the buffers of the push being applied (the pass
  * reads them before the selection writes).
  *   push_*, grads, clients, grad_ts, K  as for fasgd_apply_with_push

@@ -565,6 +565,9 @@ namespace {
 // against 236 us, 8 301 against 298, 32 760 against 736; 100M, K = 4 903
 // against 937, 8 1189 against 1189, 32 3042 against 2958; 2M, K = 8 36.0
 // against 33.3, 32 74.1 against 67.7.
+// Not where v or the gradient is only 4-byte aligned, whose mark reads one
+// parameter per load: 25M, K = 8 361 in the pass against 391 us apart, 16 542
+// against 554, 32 879 against 906; 100M, K = 8 1433 against 1551.
 constexpr int kDecideApartFrom = 8;
 }  // namespace
 
@@ -597,7 +600,7 @@ fasgd_status fasgd_apply_with_push_and_select(fasgd_state* st, const int32_t* pu
     if (s != FASGD_OK) return s;
     // the pass takes the decisions and the selection's own launches scan them
     // and scatter, or the selection follows whole
-    const bool apart = st->math_mode == FASGD_MATH_IEEE && K >= kDecideApartFrom;
+    const bool apart = st->math_mode == FASGD_MATH_IEEE && K >= kDecideApartFrom && sel_vec;
     hipError_t e = pass_begin(stream);
     if (e == hipSuccess) e = fasgd::launch_fasgd_dense_push(a, p, apart ? nullptr : &m, variant_of(st), vec, stream);
     if (e == hipSuccess) e = pass_end(stream);

@@ -45,3 +45,40 @@ def test_step_equals_two_calls(P, off, K):
         out.append([st.tensors[n].view(torch.int32) for n in ("theta", "n", "b", "v")] + [idx[:m], val[:m].view(torch.int32), seg])
     for x, y in zip(*out):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("K", [8, 32])
+def test_step_of_a_misaligned_state_equals_two_calls(K):
+    """Statistics 4 bytes past a 16-byte boundary, gradients on one: the decisions stay in the pass."""
+    import torch
+    dev = gpu()
+    P = 5003
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(K)
+    theta0 = torch.randn(P, device=dev, generator=gen)
+    grads = [torch.randn(P, device=dev, generator=gen) * 1e-2 for _ in range(K + 2)]
+    clients, L = [k % 4 for k in range(K)], fa.bfasgd_list_index_length(P)
+    out = []
+    for together in (True, False):
+        views = [x[1:] for x in fa.allocate_state(P + 1, dev)]
+        views[0].copy_(theta0)
+        st = fa.fasgd_init_state(*views, lam=4, alpha=0.005, math_mode=fa.MATH_IEEE, v0=3.0)
+        st.c.T, st.c.dense_T = 60, 59
+        idx, val = torch.zeros(P, device=dev, dtype=torch.int32), torch.zeros(P, device=dev)
+        cnt = torch.zeros(1, device=dev, dtype=torch.int64)
+        seg = torch.zeros(L, device=dev, dtype=torch.int32)
+        ws = torch.empty(fa.bfasgd_workspace_bytes(P), device=dev, dtype=torch.uint8)
+        fa.bfasgd_select_compact(st, grads[K], 20.0, 1e-8, 9, st.T, 1, idx, val, cnt, ws, seg_start=seg)
+        ts = [61 + k - k % 3 for k in range(K)]
+        if together:
+            fa.fasgd_apply_with_push_and_select(st, idx, val, cnt, seg, 1, 58, grads[:K], clients, ts, grads[K + 1], 2,
+                                                20.0, 1e-8, 9, idx, val, cnt, seg, ws)
+        else:
+            fa.fasgd_apply_with_push(st, idx, val, cnt, seg, 1, 58, grads[:K], clients, ts)
+            fa.bfasgd_select_compact(st, grads[K + 1], 20.0, 1e-8, 9, st.T, 2, idx, val, cnt, ws, seg_start=seg)
+        torch.cuda.synchronize()
+        m = int(cnt.item())
+        assert 0 < m < P and st.T == 61 + K
+        out.append([st.tensors[n].view(torch.int32) for n in ("theta", "n", "b", "v")] + [idx[:m], val[:m].view(torch.int32), seg])
+    for x, y in zip(*out):
+        assert torch.equal(x, y)
