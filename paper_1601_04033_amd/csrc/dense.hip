@@ -54,7 +54,20 @@ static_assert(kIeeeBatch == kPushBatch, "the pass with a push hands its first ba
 // 300k, K = 8 5.6, 5.1, 5.2 us; 300k, K = 32 12.1, 11.1, 10.3; 700k, K = 32
 // 22.9, 21.6, 21.1; 1M, K = 24 22.9, 22.9, 23.4; 1.8M, K = 16 31.5, 30.4, 30.8;
 // 2.5M, K = 24 54.3, 55.1, 55.2.
-constexpr int lane_batch(int64_t P) { return P <= 500'000 ? 8 : P <= 2'000'000 ? 4 : kLaneBatch; }
+// Fewer gradients than that batch go one guarded load and update after the
+// other (load_rest), which in the shortest passes costs more than a smaller
+// batch that they fill.  Replayed from a graph, batches of 8 and of what
+// stands here: 20k, K = 1 2.46 and 2.43 us, 3 2.56 and 2.43, 5 2.80 and 2.57, 7
+// 2.98 and 2.72; 200k, K = 3 3.31 and 3.13; but 400k, K = 3 4.15, 4.53 in a batch
+// of 3, and 100k, K = 7 3.41, 3.52 in batches of 4.  1.8M, K = 3: 15.0 in a batch
+// of 4, 14.6 in one of 3.
+constexpr int lane_batch(int64_t P, int K)
+{
+    if (P <= 200'000 && K <= 3) return kLaneBatch;
+    if (P <= 50'000 && K < 8) return 4;
+    if (P <= 500'000) return 8;
+    return P <= 2'000'000 && K != 3 ? 4 : kLaneBatch;
+}
 unsigned lane_grid(int64_t P) { return static_cast<unsigned>((P + kLaneBlock - 1) / kLaneBlock); }
 
 __device__ __forceinline__ f4 ld4(const float* p)
@@ -93,7 +106,8 @@ __device__ __forceinline__ void pass_step(float& th, float& n, float& b, float& 
 }
 
 // The gradients from k on (fewer than a batch) at parameter j, every load
-// before the first use: one at a time, each waited for the one before it
+// before the first use (one branch per gradient that is there, not per place
+// in the batch): one at a time, each waited for the one before it
 // (25M parameters, K = 2: 169 -> 155 us; K = 8: 246 -> 241; 12M, K = 5:
 // 100 -> 97; SASGD at 25M, K = 3: 113 -> 89).  Not in the pass with a push,
 // where it lost (the 25M step with K = 2 197 -> 213 us, with K = 5 245 -> 257).
@@ -101,8 +115,10 @@ template <int N>
 __device__ __forceinline__ void load_rest(const DenseArgs& a, int64_t j, int k, float (&g)[N])
 {
 #pragma unroll
-    for (int u = 0; u < N; ++u)
-        if (k + u < a.K) g[u] = ldnt(a.grad[k + u] + j);
+    for (int u = 0; u < N; ++u) {
+        if (k + u >= a.K) break;
+        g[u] = ldnt(a.grad[k + u] + j);
+    }
 }
 
 unsigned grid_for(int64_t items)
@@ -699,7 +715,7 @@ __device__ __forceinline__ void lane_updates(const DenseArgs& a, int64_t j, floa
     const Hyper h = a.h;
     const int K = a.K;
     int k = 0;
-    if (SHORT && K >= kIeeeBatch) {
+    if (SHORT) {   // K >= kIeeeBatch
         float g[kIeeeBatch];
 #pragma unroll
         for (int u = 0; u < kIeeeBatch; ++u) g[u] = ldnt(a.grad[u] + j);
@@ -716,20 +732,26 @@ __device__ __forceinline__ void lane_updates(const DenseArgs& a, int64_t j, floa
     float g[BATCH - 1];
     load_rest(a, j, k, g);
 #pragma unroll
-    for (int u = 0; u < BATCH - 1; ++u)
-        if (k + u < K) pass_step<MODE, SHORT>(th, n, b, v, g[u], a.coef[k + u], h);
+    for (int u = 0; u < BATCH - 1; ++u) {
+        if (k + u >= K) break;
+        pass_step<MODE, SHORT>(th, n, b, v, g[u], a.coef[k + u], h);
+    }
 }
 
 // K-fused FASGD, one parameter per thread (any 4-byte alignment): the pass
-// for every P below kMaxScalarItems.
-template <int MODE, int BATCH>
+// for every P below kMaxScalarItems.  SHORT: an IEEE pass of K >= kIeeeBatch.
+// Passes of fewer gradients are bound by their loads and look at each divisor:
+// the look at v would hold the gradients' loads back until v is there, and
+// the three bodies of the short form cost instruction fetches (IEEE, K = 3:
+// 400k 4.77 -> 4.28 us, 1M 9.19 -> 8.93, 25M 169 -> 167; K = 1: 25M 147 -> 137).
+template <int MODE, int BATCH, bool SHORT>
 __global__ __launch_bounds__(kLaneBlock) void fasgd_dense_lane(const DenseArgs a)
 {
     const int64_t j = static_cast<int64_t>(blockIdx.x) * kLaneBlock + threadIdx.x;
     if (j >= a.P) return;
     float th = ldnt(a.theta + j), n = ldnt(a.n + j), b = ldnt(a.b + j), v = ldnt(a.v + j);
-    if (short_pass<MODE>(v, a.h)) {
-        lane_updates<MODE, BATCH, true>(a, j, th, n, b, v);
+    if (SHORT && short_pass<MODE>(v, a.h)) {
+        lane_updates<MODE, BATCH, SHORT>(a, j, th, n, b, v);
         if (__builtin_expect(__ballot(v != v) != 0, 0)) {   // an infinite or NaN x: the pass again, divisor by divisor
             th = a.theta[j]; n = a.n[j]; b = a.b[j]; v = a.v[j];
             lane_updates<MODE, BATCH, false>(a, j, th, n, b, v);
@@ -874,11 +896,14 @@ PushArgs readable_list(const PushArgs& p)
 template <int VARIANT>
 void launch_dense_variant(const DenseArgs& a, hipStream_t s)
 {
-    if (a.P <= kMaxScalarItems) {
-        switch (lane_batch(a.P)) {
-        case 8: fasgd_dense_lane<VARIANT, 8><<<lane_grid(a.P), kLaneBlock, 0, s>>>(a); break;
-        case 4: fasgd_dense_lane<VARIANT, 4><<<lane_grid(a.P), kLaneBlock, 0, s>>>(a); break;
-        default: fasgd_dense_lane<VARIANT, kLaneBatch><<<lane_grid(a.P), kLaneBlock, 0, s>>>(a);
+    constexpr bool ieee = (VARIANT & MATH_FAST) == 0;
+    if (a.P <= kMaxScalarItems && ieee && a.K < kIeeeBatch) {
+        fasgd_dense_lane<VARIANT, kLaneBatch, false><<<lane_grid(a.P), kLaneBlock, 0, s>>>(a);
+    } else if (a.P <= kMaxScalarItems) {
+        switch (lane_batch(a.P, a.K)) {
+        case 8: fasgd_dense_lane<VARIANT, 8, ieee><<<lane_grid(a.P), kLaneBlock, 0, s>>>(a); break;
+        case 4: fasgd_dense_lane<VARIANT, 4, ieee><<<lane_grid(a.P), kLaneBlock, 0, s>>>(a); break;
+        default: fasgd_dense_lane<VARIANT, kLaneBatch, ieee><<<lane_grid(a.P), kLaneBlock, 0, s>>>(a);
         }
     } else {
         fasgd_dense_vec<VARIANT><<<grid_for((a.P >> 2) + 1), kBlock, 0, s>>>(a);

@@ -54,3 +54,26 @@ def test_sync_step_equals_sasgd_on_divided_gradients(lam):
     fa.sasgd_apply_updates(plain, divided, list(range(lam)), list(range(lam)))   # every tau 0
     torch.cuda.synchronize()
     assert torch.equal(sync.tensors["theta"].view(torch.int32), plain.tensors["theta"].view(torch.int32))
+
+
+@pytest.mark.parametrize("P", [50_000, 50_001, 200_000, 200_001])
+@pytest.mark.parametrize("rule", ["fast", "ieee"])
+def test_short_passes_equal_one_pass_per_gradient(P, rule):
+    """The sizes where the batch of a pass of few gradients changes."""
+    import torch
+    dev = gpu()
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(P)
+    theta0 = torch.randn(P, device=dev, generator=gen)
+    grads = [torch.randn(P, device=dev, generator=gen) * 1e-2 for _ in range(9)]
+    mode = fa.MATH_IEEE if rule == "ieee" else fa.MATH_FAST
+    for K in (1, 2, 3, 4, 5, 7, 8, 9):
+        one, each = new_gpu_state(theta0, dev, 4, 0.005, mode), new_gpu_state(theta0, dev, 4, 0.005, mode)
+        clients, ts = [k % 4 for k in range(K)], [k - k % 3 for k in range(K)]
+        fa.fasgd_apply_updates(one, grads[:K], clients, ts)
+        for k in range(K):
+            fa.fasgd_apply_updates(each, grads[k:k + 1], clients[k:k + 1], ts[k:k + 1])
+        torch.cuda.synchronize()
+        for name in ("theta", "n", "b", "v"):
+            x, y = one.tensors[name], each.tensors[name]
+            assert torch.equal(x.view(torch.int32), y.view(torch.int32)), (name, K)
