@@ -947,6 +947,9 @@ __global__ __launch_bounds__(kListBlock) void sparse_apply(const SparseArgs a)
 // for sparse_apply.  Selection and copy together, plain E = 1 (the former
 // form), plain E = 2, STREAM with E = 2 and with E = 1, same box:
 //   P, transmitted   E = 1    E = 2    E = 2 s. E = 1 s.
+//   100k, 1 %        9.05     9.45 us
+//   1M, 20 %         10.9     11.1
+//   1.8M, 2 %        12.4     12.2
 //   4M, 10 %         18.2     16.6     18.9     18.5 us
 //   8M, 5 %          27.1     23.9     26.8     26.2
 //   8M, 30 %         40.1     37.6     35.3     36.2
@@ -1109,9 +1112,13 @@ void launch_scatter_shape(float* dst, int64_t P, const int32_t* idx, const float
 hipError_t launch_scatter(float* dst, int64_t P, const int32_t* idx, const float* val,
                           const int64_t* d_count, int64_t capacity, hipStream_t s)
 {
-    // by the size of dst: up to 40 MB, about the L2 caches, and up to 160 MB,
-    // inside the Infinity Cache (see scatter_list for both sides of each line)
-    if (P <= 10'000'000)
+    // by the size of dst: up to 6 MB, where most of the grid has no entry and
+    // one per lane is the shorter chain; up to 40 MB, about the L2 caches; and
+    // up to 160 MB, inside the Infinity Cache (see scatter_list for both sides
+    // of each line)
+    if (P <= 1'500'000)
+        launch_scatter_shape<1, false>(dst, P, idx, val, d_count, capacity, s);
+    else if (P <= 10'000'000)
         launch_scatter_shape<2, false>(dst, P, idx, val, d_count, capacity, s);
     else if (P <= 40'000'000)
         launch_scatter_shape<2, true>(dst, P, idx, val, d_count, capacity, s);

@@ -37,3 +37,18 @@ def test_list_copies(P, density):
             got = copy.clone()
             fa.bfasgd_apply_fetch(got, idx[:cut].contiguous(), val[:cut].contiguous(), cnt, seg_start=index)
             assert torch.equal(got, want), (P, density, index is not None, "cut")
+
+
+@pytest.mark.parametrize("P", [1_499_999, 1_500_000, 1_500_001])
+def test_scattered_copies_around_one_entry_per_lane(P):
+    import torch
+    dev = gpu()
+    gen = torch.Generator(device=dev).manual_seed(P)
+    copy = torch.randn(P, device=dev, generator=gen)
+    for m in (1, 63, 64, 65, 255, 256, 257, P // 3):
+        listed = torch.randperm(P, device=dev, generator=gen)[:m]
+        val = torch.randn(m, device=dev, generator=gen)
+        got, want = copy.clone(), copy.clone()
+        want[listed] = val
+        fa.bfasgd_apply_fetch(got, listed.int(), val, torch.full((1,), m, device=dev, dtype=torch.int64))
+        assert torch.equal(got, want), m
