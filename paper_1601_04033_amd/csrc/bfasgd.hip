@@ -1109,17 +1109,29 @@ void launch_scatter_shape(float* dst, int64_t P, const int32_t* idx, const float
     scatter_list<E, STREAM><<<static_cast<unsigned>(g), kListBlock, 0, s>>>(dst, P, idx, val, d_count, capacity);
 }
 
+// By the size of dst: up to 6 MB, where most of the grid has no entry and one
+// per lane is the shorter chain; up to 40 MB, about the L2 caches; and up to
+// 160 MB, inside the Infinity Cache (see scatter_list for both sides of each
+// line).  Where the next launch reads dst whole, lines that stay in a cache
+// are not read from HBM again, and the stores are plain until dst is far
+// larger than the Infinity Cache.  A cached push without an index, STREAM as
+// by the lines above against plain E = 1 and 2, same box:
+//   P, transmitted   STREAM   E = 1    E = 2
+//   12M, 10 %        111      116      109 us
+//   25M, 30 %        237      232      231
+//   39M, 30 %        377      350      356
+//   60M, 10 %        533      509      515
+//   100M, 30 %       953      942      942
+//   300M, 10 %       2649     2710     2712
 hipError_t launch_scatter(float* dst, int64_t P, const int32_t* idx, const float* val,
-                          const int64_t* d_count, int64_t capacity, hipStream_t s)
+                          const int64_t* d_count, int64_t capacity, bool read_next, hipStream_t s)
 {
-    // by the size of dst: up to 6 MB, where most of the grid has no entry and
-    // one per lane is the shorter chain; up to 40 MB, about the L2 caches; and
-    // up to 160 MB, inside the Infinity Cache (see scatter_list for both sides
-    // of each line)
     if (P <= 1'500'000)
         launch_scatter_shape<1, false>(dst, P, idx, val, d_count, capacity, s);
-    else if (P <= 10'000'000)
+    else if (P <= (read_next ? 30'000'000 : 10'000'000))
         launch_scatter_shape<2, false>(dst, P, idx, val, d_count, capacity, s);
+    else if (read_next && P <= 150'000'000)
+        launch_scatter_shape<1, false>(dst, P, idx, val, d_count, capacity, s);
     else if (P <= 40'000'000)
         launch_scatter_shape<2, true>(dst, P, idx, val, d_count, capacity, s);
     else

@@ -745,7 +745,7 @@ fasgd_status bfasgd_apply_cached(fasgd_state* st, const int32_t* idx, const floa
         return ok();
     }
     if (capacity > 0) {
-        const hipError_t e = fasgd::launch_scatter(cache, st->P, idx, val, d_count, capacity, stream);
+        const hipError_t e = fasgd::launch_scatter(cache, st->P, idx, val, d_count, capacity, true, stream);
         if (e != hipSuccess) return hip_fail(e, "bfasgd_apply_cached (cache update)");
     }
     fasgd::DenseArgs a;
@@ -791,7 +791,7 @@ fasgd_status bfasgd_apply_fetch(float* theta_client, int64_t P, const int32_t* i
         return ok();
     }
     if (capacity > 0) {
-        const hipError_t e = fasgd::launch_scatter(theta_client, P, idx, val, d_count, capacity, stream);
+        const hipError_t e = fasgd::launch_scatter(theta_client, P, idx, val, d_count, capacity, false, stream);
         if (e != hipSuccess) return hip_fail(e, "bfasgd_apply_fetch");
     }
     return ok();

@@ -212,8 +212,8 @@ hipError_t launch_seg_decide(const SegGroup& g, const float* v, double* partial,
 hipError_t launch_seg_apply(SegGroup& g, const SegApplyArgs& a, int variant, hipStream_t s);
 
 // dst[idx[i]] = val[i] for i < min(*d_count, capacity); indices outside
-// [0, P) are skipped.
+// [0, P) are skipped.  read_next: the next launch reads dst whole.
 hipError_t launch_scatter(float* dst, int64_t P, const int32_t* idx, const float* val,
-                          const int64_t* d_count, int64_t capacity, hipStream_t s);
+                          const int64_t* d_count, int64_t capacity, bool read_next, hipStream_t s);
 
 }  // namespace fasgd

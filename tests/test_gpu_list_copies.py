@@ -52,3 +52,29 @@ def test_scattered_copies_around_one_entry_per_lane(P):
         want[listed] = val
         fa.bfasgd_apply_fetch(got, listed.int(), val, torch.full((1,), m, device=dev, dtype=torch.int64))
         assert torch.equal(got, want), m
+
+
+@pytest.mark.parametrize("P", [1_500_001, 30_000_000, 30_000_001, 150_000_000, 150_000_001])
+def test_cached_push_without_an_index(P):
+    """A push whose list is copied into the client's cache ahead of the pass, where the copy's form changes: the cache
+    against torch's index assignment, the state against the push with the index, which merges the list in the pass."""
+    import torch
+    from helpers import new_gpu_state
+    dev = gpu()
+    gen = torch.Generator(device=dev).manual_seed(P)
+    listed = torch.nonzero(torch.rand(P, device=dev, generator=gen) < 0.02).reshape(-1)
+    m = listed.numel()
+    val = torch.randn(m, device=dev, generator=gen)
+    theta0, cache0 = torch.randn(P, device=dev, generator=gen), torch.randn(P, device=dev, generator=gen)
+    cnt = torch.full((1,), m, device=dev, dtype=torch.int64)
+    edges = torch.arange(fa.bfasgd_list_index_length(P), device=dev) * 256
+    seg = torch.searchsorted(listed, edges.clamp_(max=P)).int()
+    out = []
+    for index in (None, seg):
+        st, cache = new_gpu_state(theta0, dev, 4, 0.005, fa.MATH_FAST, v0=3.0), cache0.clone()
+        fa.bfasgd_apply_cached(st, listed.int(), val, cnt, cache, 1, 0, seg_start=index)
+        out.append([st.tensors[n].view(torch.int32) for n in ("theta", "n", "b", "v")] + [cache])
+    for x, y in zip(*out):
+        assert torch.equal(x, y)
+    cache0[listed] = val
+    assert torch.equal(out[0][-1], cache0)
