@@ -59,14 +59,15 @@ static_assert(kIeeeBatch == kPushBatch, "the pass with a push hands its first ba
 // batch that they fill.  Replayed from a graph, batches of 8 and of what
 // stands here: 20k, K = 1 2.46 and 2.43 us, 3 2.56 and 2.43, 5 2.80 and 2.57, 7
 // 2.98 and 2.72; 200k, K = 3 3.31 and 3.13; but 400k, K = 3 4.15, 4.53 in a batch
-// of 3, and 100k, K = 7 3.41, 3.52 in batches of 4.  1.8M, K = 3: 15.0 in a batch
-// of 4, 14.6 in one of 3.
+// of 3, and 100k, K = 7 3.41, 3.52 in batches of 4.  Above 500k, in batches of 4
+// and of 3: 1.8M, K = 3 15.0 and 14.6; 600k, K = 6 7.81 and 7.53, K = 12 10.4 and
+// 10.8; 1M, K = 9 13.3 and 12.95 (K = 18 and 21 2 % apart, 600k the other way).
 constexpr int lane_batch(int64_t P, int K)
 {
     if (P <= 200'000 && K <= 3) return kLaneBatch;
     if (P <= 50'000 && K < 8) return 4;
     if (P <= 500'000) return 8;
-    return P <= 2'000'000 && K != 3 ? 4 : kLaneBatch;
+    return P <= 2'000'000 && (K % 3 != 0 || K > 9) ? 4 : kLaneBatch;
 }
 unsigned lane_grid(int64_t P) { return static_cast<unsigned>((P + kLaneBlock - 1) / kLaneBlock); }
 
