@@ -242,11 +242,31 @@ DENSE_25M_CALLS = {1: 40, 8: 20, 32: 10}
 SELECT_25M_CALLS = 128
 
 
+# IEEE math: from this many gradients on, the step's pass leaves the next
+# push's decisions to the selection after it (16-byte aligned arrays)
+IEEE_DECIDES_APART_FROM = 8
+
+
+def step_bytes(P, K, m, L, ieee):
+    """Algorithmic bytes of fasgd_apply_with_push_and_select's two parts with
+    m entries per push and a list index of L: the pass (state 16 B read + 16 B
+    write, 4 B per gradient, for the push 4 B index + 4 B value per entry and
+    its list index, and the next push's decisions, 1 bit per parameter, where
+    it takes them) and the selection after it (the decisions or v, and the
+    gradient read, (idx, val) written); and whether the pass takes the
+    decisions."""
+    in_pass = not (ieee and K >= IEEE_DECIDES_APART_FROM)
+    pass_bytes = P * (32 + 4 * K) + 8 * m + 4 * L + (P / 8 if in_pass else 0)
+    sel_bytes = P * 4 + (P / 8 if in_pass else P * 4) + m * 8
+    return pass_bytes, sel_bytes, in_pass
+
+
 def large_25m(fa, workload, dev, mode, K=32, reps=20):
     """The 25M-parameter workload (50 blocks of 500k, lambda = 64) beside the
     main one: the dense pass at K = 1, 8, 32, the server's step (one
     fasgd_apply_with_push_and_select call: a 10 % push and K gradients in one
-    pass that also takes the next push's decisions, then its compaction) and
+    pass that also takes the next push's decisions (in IEEE math the selection
+    after it does, at this K), then its compaction) and
     the selection on its own, each over calls issued back to back.  Fractions
     are algorithmic bytes over time against 8 TB/s."""
     import torch
@@ -298,7 +318,7 @@ def large_25m(fa, workload, dev, mode, K=32, reps=20):
     torch.cuda.synchronize()
     pass_ms = sum(a.elapsed_time(e) for a, e in passes[1:]) / len(passes[1:])
     m = int(cnt.item())
-    pass_bytes = P * (32 + 4 * K) + 8 * m + 4 * fa.bfasgd_list_index_length(P) + P / 8
+    pass_bytes, _, _ = step_bytes(P, K, m, fa.bfasgd_list_index_length(P), mode == fa.MATH_IEEE)
     out["step"] = {"ms": step_ms, "ms_range": step_spread, "param_updates_per_s": (P * K + m) / (step_ms * 1e-3),
                    "pass_ms": pass_ms, "pass_frac": pass_bytes / (pass_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
                    "transmitted_fraction": m / P}
@@ -587,15 +607,10 @@ def main():
     updates = steps * P * K + sum(m_list)
     value = updates / wall
     pass_ms = float(np.mean(ms["pass"])) if ms["pass"] else float("nan")
-    # per launch: state 16 B read + 16 B write, 4 B per gradient, for the
-    # push 4 B index + 4 B value per entry and its list index, and the next
-    # push's decisions (1 bit per parameter)
-    pass_bytes = P * (32 + 4 * K) + 8 * m_avg + 4 * fa.bfasgd_list_index_length(P) + P / 8
+    pass_bytes, sel_bytes, decided_in_pass = step_bytes(P, K, m_avg, fa.bfasgd_list_index_length(P), args.math == "ieee")
     achieved = pass_bytes / (pass_ms * 1e-3) / 1e9
     traffic = measured_traffic(args.workload, P, K, args.math)
     sel_ms = float(np.mean(ms["select"]))
-    # after the pass took the decisions: ballots and g read, (idx, val) written
-    sel_bytes = P * 4 + P / 8 + m_avg * 8
 
     # the same steps as three separate calls (dense pass, selection, sparse
     # apply), for comparison
@@ -770,8 +785,10 @@ def main():
         "data": "synthetic",
         "config": {"workload": f"{args.workload}: {w.name}, P={P}, lambda={w.lam}, per step one call: a pass "
                                f"applying the previous B-FASGD push (~{int(f * 100)}% transmitted) and K={K} "
-                               f"FASGD updates and taking the next push's transmit decisions, then that push's "
-                               f"compaction; {args.math} math",
+                               + ("FASGD updates and taking the next push's transmit decisions, then that push's "
+                                  "compaction" if decided_in_pass else
+                                  "FASGD updates, then the next push's decisions and compaction") +
+                               f"; {args.math} math",
                    "P": P, "K": K, "lambda": w.lam, "math": args.math, "transmit_fraction": f, "c": c},
         "roofline": {"bound": "hbm", "kernel": "fasgd_dense_push_lane", "achieved": achieved,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,

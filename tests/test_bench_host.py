@@ -88,3 +88,17 @@ def test_grouped_timing_reports_the_median_group():
     ms, (lo, hi) = bench.grouped_b2b(fake, fn, 10)
     assert calls[0] == 1 + 5 * 10
     assert ms == pytest.approx(0.6) and lo == pytest.approx(0.6) and hi == pytest.approx(10.6)
+
+
+def test_step_bytes_follow_the_library_s_rule():
+    """IEEE steps of 8 gradients or more decide after the pass: their pass writes no decisions, their selection reads v."""
+    import re
+    src = open(os.path.join(ROOT, "paper_1601_04033_amd", "csrc", "fasgd_api.hip")).read()
+    assert int(re.search(r"kDecideApartFrom = (\d+);", src).group(1)) == bench.IEEE_DECIDES_APART_FROM
+    P, m, L = 1 << 20, 1000, 4097
+    for K in (1, 7, 8, 32):
+        for ieee in (False, True):
+            pass_bytes, sel_bytes, in_pass = bench.step_bytes(P, K, m, L, ieee)
+            assert in_pass == (K < 8 or not ieee)
+            assert pass_bytes == P * (32 + 4 * K) + 8 * m + 4 * L + (P // 8 if in_pass else 0)
+            assert sel_bytes == 4 * P + 8 * m + (P // 8 if in_pass else 4 * P)
