@@ -487,15 +487,22 @@ fasgd_status fasgd_copy_anchor(const float* src, float* dst, int64_t n, hipStrea
  * 1 / sqrt(x) as two correctly rounded operations, and alpha / (v tau)
  * (Sec. 2.2's equations for v and the rate).  When eps >= 2^-96 (finite) and
  * 2^-20 <= |alpha| < 2^20 the kernels take shorter sequences (a hardware
- * estimate, then corrections by exact fma residuals); this call compares them
- * with the general sequences:
- *   d_mismatches[0]  sqrt over every float x >= 2^-96 (+inf and NaNs too);
- *   d_mismatches[1]  1 / sqrt(x) over the same x;
- *   d_mismatches[2]  alpha / d over all 2^32 bit patterns of d;
+ * estimate, then corrections by exact fma residuals) wherever their operands
+ * lie in the ranges below, and the general ones elsewhere; this call compares
+ * the two over those ranges:
+ *   d_mismatches[0]  sqrt over every finite float x >= 2^-96 (for x = +inf or
+ *                    NaN the short root must be NaN, by which an update finds
+ *                    such an x);
+ *   d_mismatches[1]  1 / sqrt(x) over the same finite x;
+ *   d_mismatches[2]  alpha / d over every d with 2^-100 <= |d| <= 2^100 (every
+ *                    other bit pattern of d must be found out of range);
  *   d_mismatches[3]  n_updates whole updates in both readings of v, on
  *                    pseudo-random states drawn from `seed` (zeros,
- *                    subnormals, infinities and NaNs among them), with
- *                    gamma, beta, eps and alpha.
+ *                    subnormals, infinities and NaNs among them, so the
+ *                    general sequences too), with gamma, beta, eps and alpha;
+ *                    and, where v starts in the range from which a pass looks
+ *                    at no divisor, the update of such a pass, which must
+ *                    agree or leave v NaN (the pass then runs again).
  * NaN results count as equal to NaN results.  d_mismatches: device, 4
  * counters (8-byte aligned), cleared by the call, read after the stream is
  * synchronised; all four are 0 when the sequences hold.  FASGD_ERR_ARG when

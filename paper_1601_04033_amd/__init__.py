@@ -529,9 +529,11 @@ def fasgd_copy_anchor(src, dst, stream=None) -> None:
 def fasgd_check_ieee_sequences(gamma: float, beta: float, eps: float, alpha: float, seed: int, n_updates: int,
                                mismatches, stream=None) -> None:
     """Diagnostics: compare, on the device, the IEEE update's short correctly
-    rounded sequences with the general ones, bit for bit; the four mismatch
-    counts go to `mismatches` (int64 [4], device): square root, 1/sqrt, the
-    division alpha / d over every d, and n_updates whole updates."""
+    rounded sequences with the general ones, bit for bit, over the operands
+    they are used for; the four mismatch counts go to `mismatches` (int64 [4],
+    device): square root and 1/sqrt over every finite x >= 2^-96, the division
+    alpha / d over every |d| in [2^-100, 2^100], and n_updates whole updates,
+    which hold infinities and NaNs too."""
     import torch
     if mismatches.numel() < 4:
         raise ValueError("mismatches needs 4 counters")

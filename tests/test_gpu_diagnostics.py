@@ -23,8 +23,11 @@ SETTINGS = [(0.95, 0.9, 1e-4, 0.005), (0.95, 0.9, 1e-8, 0.04), (0.5, 0.5, 9 / 16
 
 @pytest.mark.parametrize("gamma,beta,eps,alpha", SETTINGS)
 def test_short_sequences_equal_general_ones(gamma, beta, eps, alpha):
-    """Square root and 1/sqrt over every float x >= 2^-96, alpha / d over all
-    2^32 bit patterns of d, and 2^24 whole updates per reading of v."""
+    """Square root and 1/sqrt over every finite float x >= 2^-96 (an infinite
+    or NaN x gives a NaN root), alpha / d over every d of the short range with
+    either sign (every other of the 2^32 bit patterns is found to be outside
+    it), and 2^24 whole updates per reading of v, infinities and NaNs among
+    their states."""
     import torch
     dev = gpu()
     counts = torch.full((4,), -1, dtype=torch.int64, device=dev)

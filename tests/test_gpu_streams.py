@@ -29,8 +29,9 @@ def _selection_case(P, seed, c, dev):
 
 def test_selections_on_two_streams_match_the_oracle():
     """A two-launch selection (3M parameters) and a three-launch one (52M,
-    whose scan counts arrivals in its workspace) repeated back to back on two
-    streams at once: each list, count and list index is the oracle's."""
+    whose scatter sums the totals that its scan left in the workspace)
+    repeated back to back on two streams at once: each list, count and list
+    index is the oracle's."""
     import torch
     dev = gpu()
     cases = [(3_000_017, 11, 30.0), (52_000_003, 12, 60.0)]
