@@ -409,8 +409,9 @@ fasgd_status bfasgd_apply_cached(fasgd_state* st, const int32_t* idx, const floa
  *                 one partial sector per entry: faster when most segments
  *                 hold an entry (above a few percent transmitted) and the
  *                 copy does not fit the 256 MB Infinity Cache (1e9
- *                 parameters at 10 %: 1.5 against 2.0 ms), slower otherwise
- *                 (1e9 at 1 %: 0.73 against 0.43 ms).  The result is the same.
+ *                 parameters at 10 %: 1.3 against 1.7 ms), slower where few
+ *                 do (1e9 at 1 %: 1.2 against 0.41 ms).  The result is the
+ *                 same.
  */
 fasgd_status bfasgd_apply_fetch(float* theta_client, int64_t P, const int32_t* idx, const float* val,
                                 const int64_t* d_count, const uint32_t* seg_start, int64_t capacity,

@@ -873,6 +873,8 @@ constexpr int64_t kListMaxBlocks = 65536;     // grid cap of the list kernels (g
 //   300M, 10 %       3280     3090     2800
 //   300M, 2 %        1632     1566     1549
 // (non-temporal loads of the state cost 30 %: a line's second reader misses).
+// The lines are drawn at 10 %, by P alone: the launch does not know the count,
+// and at 25M and 30 % E = 6 still beats the plain form.
 template <int MODE, int E, bool STREAM>
 __device__ __forceinline__ void sparse_runs(const SparseArgs& a, int64_t m)
 {
@@ -956,6 +958,8 @@ __global__ __launch_bounds__(kListBlock) void sparse_apply(const SparseArgs a)
 //   20M, 20 %        86.2     81.9     77.7     80.2
 //   60M, 10 %        218      221      200      196
 //   60M, 30 %        242      257      235      226
+// (by P alone, as the launch does not know the count: at 8M and 30 % the
+// streaming form would gain 6 %, at 5 % it would lose 12)
 template <int E, bool STREAM>
 __global__ __launch_bounds__(kListBlock) void scatter_list(float* __restrict__ dst, int64_t P,
                                                        const int32_t* __restrict__ idx,

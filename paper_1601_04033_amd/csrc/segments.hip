@@ -148,7 +148,8 @@ __global__ __launch_bounds__(kDecideThreads) void seg_decide(const SegGroup g, c
 // where a segment starts off a multiple of 4 (decision and apply together,
 // same box): 25M in 16 segments 220 -> 188 us, 40M whole 334 -> 306, 5M in
 // 50 79.7 -> 64.6, the MLP's 6 tensors 21.6 -> 20.2, 300k in 6 14.4 -> 13.8
-// (15.2 in the streaming form; the MLP 21.0 in the other).
+// (15.2 in the streaming form; the MLP 21.0 in the other).  Only these two of
+// the four combinations were timed.
 constexpr int64_t kStreamBytes = int64_t(32) << 20;   // the eight L2 caches together
 typedef int i4 __attribute__((ext_vector_type(4)));
 
