@@ -154,9 +154,9 @@ def _native():
             if m.TORCH_VERSION != torch.__version__:
                 raise ImportError(f"built with torch {m.TORCH_VERSION}, not {torch.__version__}")
         except ImportError as e:
+            _calls = _GeneralWay()
             warnings.warn(f"_marshal.so is not built or does not load ({e}): calls are marshalled in Python, "
                           "30 us slower at 32 gradients; run __graft_entry__.build()", RuntimeWarning, stacklevel=3)
-            _calls = _GeneralWay()
             return _calls
         m.bind([ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in m.ENTRY_POINTS], _current_stream)
         _calls = m
